@@ -170,7 +170,7 @@ struct Plan {
   Capacity cap;
   long long s_n, s_z, s_zp, s_sig, s_ell, s_E, s_m, s_apart, s_gpart, s_e2, s_om, s_eb, s_pc, s_bd, s_y, s_cl,
       s_cov, s_sel, s_ord, s_pool, s_spart, s_bat, s_slot, s_sup, s_cos, s_del, s_ftag, s_gate,
-      s_pi, s_st, s_keys, s_u, s_cnt, s_rstat, s_lstat, s_tu, s_ts, s_tc, s_lpart, s_lcnt;
+      s_pi, s_st, s_keys, s_u, s_cnt, s_rstat, s_lstat, s_tu, s_ts, s_tc, s_tp, s_lpart, s_lcnt;
   long long s_gpart1, s_n2h, s_img, s_imgcnt;
   long long s_cgain, s_cscore, s_cpool, s_cbat, s_cpart, s_cert, s_dstat;
 };
@@ -236,9 +236,11 @@ Plan make_plan(const gmc_config& c) {
   pl.s_lstat = static_cast<long long>(c.landmarks) * c.landmarks * k.I;
   pl.s_img = k.N;
   pl.s_imgcnt = kMaxImages;
-  pl.s_tu = 2LL * k.N;
-  pl.s_ts = 2 * 64 * cdiv(k.ldM, 64) + 2 * 64;   // chunk partials, then the published pool
-  pl.s_tc = 2LL * (k.ldM + kMaxPersist);
+  // hand-off buffers of the persistent selection
+  pl.s_tu = 2LL * handoff_stride(k.N);
+  pl.s_ts = 2 * 64 * cdiv(k.ldM, 64);
+  pl.s_tc = 2LL * handoff_stride(k.ldM);
+  pl.s_tp = 2 * 64;
   // certificate buffers: rounds of the smallest batch size, at most
   // kCertMaxRounds
   k.cert_rounds = static_cast<int>(std::min<long long>(
@@ -295,9 +297,11 @@ size_t carve(const Plan& pl, char* base, Ws* ws) {
   ws->keys = reinterpret_cast<uint32_t*>(take(pl.s_keys, 4)); ws->s_keys = pl.s_keys;
   ws->u = reinterpret_cast<float*>(take(pl.s_u, 4)); ws->s_u = pl.s_u;
   ws->cnt = reinterpret_cast<int*>(take(pl.s_cnt, 4)); ws->s_cnt = pl.s_cnt;
-  ws->tu = reinterpret_cast<unsigned long long*>(take(pl.s_tu, 8)); ws->s_tu = pl.s_tu;
-  ws->ts = reinterpret_cast<unsigned long long*>(take(pl.s_ts, 8)); ws->s_ts = pl.s_ts;
+#define U(name) ws->name = reinterpret_cast<uint32_t*>(take(pl.s_##name, 4)); ws->s_##name = pl.s_##name
+  U(tu); U(ts);
+#undef U
   ws->tc = reinterpret_cast<unsigned long long*>(take(pl.s_tc, 8)); ws->s_tc = pl.s_tc;
+  ws->tp = reinterpret_cast<unsigned long long*>(take(pl.s_tp, 8)); ws->s_tp = pl.s_tp;
   F(rstat); F(lstat);
   ws->cert_rounds = pl.cap.cert_rounds;
   F(cgain); F(cscore); I(cpool); I(cbat); F(cpart); F(cert); F(dstat);

@@ -116,11 +116,13 @@ struct Ws {
   int* cnt;        long long s_cnt;     // completion counters          [kCounters]
   float* rstat;    long long s_rstat;   // large-pool row statistics    [3][ldM]
   float* lstat;    long long s_lstat;   // landmark min distance        [L*L]
-  // persistent selection: values tagged with (round + 1) in the high word,
-  // double-buffered by round parity; zeroed at the start of every call
-  unsigned long long* tu; long long s_tu;  // tagged gains               [2][N]
-  unsigned long long* ts; long long s_ts;  // tagged score partials [2][ceil(M/64)][64], then the pool [2][64]
-  unsigned long long* tc; long long s_tc;  // tagged coverage + heartbeats [2][ldM + kMaxPersist]
+  // persistent selection: hand-off words double-buffered by round parity,
+  // zeroed at the start of every call; the floats carry the round's tag in
+  // their sign bit
+  uint32_t* tu; long long s_tu;            // gains                      [2][handoff_stride(N)]
+  uint32_t* ts; long long s_ts;            // score partials             [2][ceil(M/64)][64]
+  unsigned long long* tc; long long s_tc;  // coverage, round + 1 in the high word [2][handoff_stride(M)]
+  unsigned long long* tp; long long s_tp;  // the batch, round + 1 in the high word [2][64]
   // diagnostics (certificate of the selection rounds, exported statistics);
   // the per-round buffers are indexed flat as (p * rounds + r) * row, so a
   // call of at most cert_rounds rounds fits
@@ -133,6 +135,10 @@ struct Ws {
   float* cert;     long long s_cert;    // per-round certificate        [cert_rounds][kCertFields] + c_B
   float* dstat;    long long s_dstat;   // exported statistics          [kStats]
 };
+
+// Words of one round's hand-off buffer: whole 256-byte pieces, so that no two
+// blocks' pieces of 64 words share a cache line in either round's buffer.
+__host__ __device__ inline int handoff_stride(int n) { return (n + 63) & ~63; }
 
 // Per-round outputs of the selection kernels (all optional): pools and
 // batches as the trace lays them out, the gains of every token and the pool
@@ -157,15 +163,15 @@ __device__ __forceinline__ void raise_status(int* cnt, unsigned bits) {
 __device__ __forceinline__ void call_init_range(const Shape& sh, const Ws& ws, int p, int x0, int stride) {
   for (int i = x0; i < sh.N; i += stride) {
     ws.sel[p * ws.s_sel + i] = -1;
-    ws.tu[p * ws.s_tu + i] = 0ull;
-    ws.tu[p * ws.s_tu + sh.N + i] = 0ull;
   }
+  for (int j = x0; j < 2 * handoff_stride(sh.N); j += stride) ws.tu[p * ws.s_tu + j] = 0u;
   for (int m = x0; m < sh.ldM; m += stride) {
     ws.cov[p * ws.s_cov + m] = 0.f;
     if (m >= sh.m) ws.alpha[p * ws.s_m + m] = 0.f;
   }
-  for (int j = x0; j < 128 * ((sh.m + 63) / 64) + 128; j += stride) ws.ts[p * ws.s_ts + j] = 0ull;
-  for (int j = x0; j < 2 * (sh.ldM + kMaxPersist); j += stride) ws.tc[p * ws.s_tc + j] = 0ull;
+  for (int j = x0; j < 128 * ((sh.m + 63) / 64); j += stride) ws.ts[p * ws.s_ts + j] = 0u;
+  for (int j = x0; j < 2 * handoff_stride(sh.m); j += stride) ws.tc[p * ws.s_tc + j] = 0ull;
+  for (int j = x0; j < 128; j += stride) ws.tp[p * ws.s_tp + j] = 0ull;
   for (int j = x0; j < (sh.hg * sh.T + 15) / 16 * sh.hkv; j += stride) ws.lcnt[p * ws.s_lcnt + j] = 0;
   // written through: the bank stream raises its flag in these words; the
   // status word is sticky (the host clears it after reading it)

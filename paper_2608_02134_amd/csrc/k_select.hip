@@ -22,9 +22,12 @@
 // Every reduction has a fixed order, so results are bitwise repeatable.
 // Zero-gain tokens key just above excluded ones, so once gains vanish the
 // lowest source indices fill the budget.
+#include <mutex>
+
 #include "gmc_device.h"
 #include "gmc_internal.h"
 #include "gmc_kernels.h"
+#include "gmc_select.h"
 
 namespace gmc {
 
@@ -34,216 +37,6 @@ constexpr int kCpwF = 4;                // fused gains kernel: tokens per wave
 constexpr int kGainColsF = 4 * kCpwF;
 constexpr int kLdsKeys = 12288;         // pool top-k keys live in LDS up to this N
 
-// Deterministic top-k over n keys (256-thread block): the `count` largest
-// keys, equal keys resolved to the lower index.  Indices are written in
-// ascending order to out[0..count).  count must not exceed the number of
-// non-zero keys.  Radix selection of the threshold key with 8-bit digits
-// (digits shared by every key are skipped; two histogram buffers, so each
-// pass needs two block barriers), then one packed scan for the ordered
-// compaction (each thread owns a contiguous index segment).
-// hist: 512 ints of LDS, scan: >= 16 ints, bc: 2 ints.
-__device__ void block_topk256(const uint32_t* keys, int n, int count, int* out, int* hist, int* scan,
-                              int* bc) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  hist[tid] = 0;
-  hist[256 + tid] = 0;
-  uint32_t kand = 0xFFFFFFFFu, kor = 0u;
-  for (int i = tid; i < n; i += 256) {
-    const uint32_t k = keys[i];
-    kand &= k;
-    kor |= k;
-  }
-  kand = wave_and_u(kand);
-  kor = wave_or_u(kor);
-  if (lane == 0) { scan[wave] = static_cast<int>(kand); scan[4 + wave] = static_cast<int>(kor); }
-  __syncthreads();
-  kand = static_cast<uint32_t>(scan[0]) & static_cast<uint32_t>(scan[1]) & static_cast<uint32_t>(scan[2]) &
-         static_cast<uint32_t>(scan[3]);
-  kor = static_cast<uint32_t>(scan[4]) | static_cast<uint32_t>(scan[5]) | static_cast<uint32_t>(scan[6]) |
-        static_cast<uint32_t>(scan[7]);
-  const uint32_t diff = kand ^ kor;                 // bits that vary between keys
-  uint32_t mask = 0;
-  int top = 24;
-  while (top > 0 && ((diff >> top) & 0xFFu) == 0u) {
-    mask |= 0xFFu << top;
-    top -= 8;
-  }
-  uint32_t prefix = kand & mask;
-  int remaining = count, buf = 0;
-  for (int shift = top; shift >= 0; shift -= 8, buf ^= 1) {
-    int* h = hist + buf * 256;
-    for (int i = tid; i < n; i += 256) {
-      const uint32_t k = keys[i];
-      if ((k & mask) == prefix) atomicAdd(&h[(k >> shift) & 255u], 1);
-    }
-    hist[(buf ^ 1) * 256 + tid] = 0;   // read in the previous pass; used by the next one
-    __syncthreads();
-    if (wave == 0) {
-      // wave 0 scans the 256 bins from the top digit down, 4 per lane
-      int v[4], loc = 0;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) { v[q] = h[255 - (lane * 4 + q)]; loc += v[q]; }
-      int excl = wave_scan_add(loc) - loc;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (excl < remaining && remaining <= excl + v[q]) {
-          bc[0] = 255 - (lane * 4 + q);
-          bc[1] = remaining - excl;
-        }
-        excl += v[q];
-      }
-    }
-    __syncthreads();
-    prefix |= static_cast<uint32_t>(bc[0]) << shift;
-    mask |= 0xFFu << shift;
-    remaining = bc[1];
-  }
-  const uint32_t kth = prefix;
-  const int seg = (n + 255) / 256;
-  const int i0 = min(n, tid * seg), i1 = min(n, i0 + seg);
-  int gt = 0, eq = 0;
-  for (int i = i0; i < i1; ++i) {
-    const uint32_t k = keys[i];
-    gt += k > kth;
-    eq += k == kth;
-  }
-  int tot;
-  const int pre = block_exclusive_scan(gt | (eq << 16), scan, &tot);
-  int gt_b = static_cast<int>(static_cast<unsigned>(pre) & 0xFFFFu);
-  int eq_b = static_cast<int>(static_cast<unsigned>(pre) >> 16);
-  for (int i = i0; i < i1; ++i) {
-    const uint32_t k = keys[i];
-    if (k > kth) {
-      out[gt_b + min(eq_b, remaining)] = i;
-      ++gt_b;
-    } else if (k == kth) {
-      if (eq_b < remaining) out[gt_b + eq_b] = i;
-      ++eq_b;
-    }
-  }
-  __syncthreads();
-}
-
-// Register-resident variant of the same selection for small n: thread t
-// holds the keys of its contiguous index segment [t*seg, t*seg + seg) in
-// k[0..KPT) (0 past the segment; zero keys are excluded).  The radix windows
-// start at the highest bit in which the non-zero keys differ, so the first
-// histogram spreads the keys over up to 256 bins.  Passes continue until the
-// bin holding the threshold is taken whole (the selection is then every
-// non-zero key >= the resolved prefix) or every bit is resolved (the
-// threshold is one key value, its first `remaining` copies by index taken).
-// Every wave scans the histograms itself, so a radix pass needs one block
-// barrier (three histogram buffers rotate).  The block has NW >= 4 waves.
-// The selected indices are written to out[0, count) in ascending index order
-// and out[count, fill) is filled with index 0.
-// hist: 768 ints of LDS, scan: >= 3 NW ints.
-template <int KPT, int NW = 4>
-__device__ void block_topk_regs(const uint32_t (&k)[KPT], int seg, int count, int* out, int* hist, int* scan,
-                                int fill = 64) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid < 256) {
-    hist[tid] = 0;
-    hist[256 + tid] = 0;
-    hist[512 + tid] = 0;
-  }
-  uint32_t kand = 0xFFFFFFFFu, kor = 0u;
-#pragma unroll
-  for (int q = 0; q < KPT; ++q) {
-    kand &= k[q] ? k[q] : 0xFFFFFFFFu;
-    kor |= k[q];
-  }
-  kand = wave_and_u(kand);
-  kor = wave_or_u(kor);
-  if (lane == 0) { scan[wave] = static_cast<int>(kand); scan[NW + wave] = static_cast<int>(kor); }
-  __syncthreads();
-  kand = static_cast<uint32_t>(scan[0]);
-  kor = static_cast<uint32_t>(scan[NW]);
-#pragma unroll
-  for (int w = 1; w < NW; ++w) {
-    kand &= static_cast<uint32_t>(scan[w]);
-    kor |= static_cast<uint32_t>(scan[NW + w]);
-  }
-  const uint32_t diff = kand ^ kor;
-  // bits [hi, 32) are shared by every non-zero key; with no differing bit
-  // every non-zero key equals kand
-  int hi = diff ? 32 - __clz(diff) : 0;
-  uint32_t mask = hi >= 32 ? 0u : ~((1u << hi) - 1u);
-  uint32_t prefix = kand & mask;
-  int remaining = count, buf = 0;
-  while (hi > 0) {
-    const int lo = max(hi - 8, 0);
-    const uint32_t wmask = ((1u << (hi - lo)) - 1u) << lo;
-    int* h = hist + buf * 256;
-#pragma unroll
-    for (int q = 0; q < KPT; ++q)
-      if (k[q] != 0u && (k[q] & mask) == prefix) atomicAdd(&h[(k[q] & wmask) >> lo], 1);
-    const int nxt = buf == 2 ? 0 : buf + 1;
-    if (tid < 256) hist[nxt * 256 + tid] = 0;   // last read two passes ago
-    __syncthreads();
-    int v[4], loc = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) { v[q] = h[255 - (lane * 4 + q)]; loc += v[q]; }
-    const int incl = wave_scan_add(loc);
-    int excl = incl - loc;
-    const bool hit = excl < remaining && remaining <= incl;
-    int dig = 0, rem = 0, inbin = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      if (excl < remaining && remaining <= excl + v[q]) {
-        dig = 255 - (lane * 4 + q);
-        rem = remaining - excl;
-        inbin = v[q];
-      }
-      excl += v[q];
-    }
-    const int src = __ffsll(static_cast<unsigned long long>(__ballot(hit))) - 1;
-    dig = __builtin_amdgcn_readlane(dig, src);
-    rem = __builtin_amdgcn_readlane(rem, src);
-    inbin = __builtin_amdgcn_readlane(inbin, src);
-    prefix |= static_cast<uint32_t>(dig) << lo;
-    mask |= wmask;
-    remaining = rem;
-    hi = lo;
-    if (inbin == remaining) {
-      // every key of the threshold bin is taken: the selection is exactly
-      // the non-zero keys >= prefix (its unresolved bits zero)
-      remaining = count;
-      hi = 0;
-    }
-    buf = nxt;
-  }
-  const uint32_t kth = prefix;
-  int gt = 0, eq = 0;
-#pragma unroll
-  for (int q = 0; q < KPT; ++q) {
-    gt += k[q] != 0u && k[q] > kth;
-    eq += k[q] != 0u && k[q] == kth;
-  }
-  // exclusive prefix of (gt, eq) over threads: wave scans, then the wave
-  // totals (scan[2 NW, 3 NW), untouched earlier in the call) after one barrier
-  const int v = gt | (eq << 16);
-  const int incl = wave_scan_add(v);
-  if (lane == 63) scan[2 * NW + wave] = incl;
-  __syncthreads();
-  int pre = incl - v;
-  for (int w = 0; w < wave; ++w) pre += scan[2 * NW + w];
-  int gt_b = static_cast<int>(static_cast<unsigned>(pre) & 0xFFFFu);
-  int eq_b = static_cast<int>(static_cast<unsigned>(pre) >> 16);
-  const int i0 = tid * seg;
-#pragma unroll
-  for (int q = 0; q < KPT; ++q) {
-    if (k[q] == 0u) continue;
-    if (k[q] > kth) {
-      out[gt_b + min(eq_b, remaining)] = i0 + q;
-      ++gt_b;
-    } else if (k[q] == kth) {
-      if (eq_b < remaining) out[gt_b + eq_b] = i0 + q;
-      ++eq_b;
-    }
-  }
-  if (tid >= count && tid < fill) out[tid] = 0;
-  __syncthreads();
-}
 
 // ---------------------------------------------------------------------------
 // coverage refresh with a batch
@@ -390,83 +183,6 @@ __global__ void __launch_bounds__(64 * kPoolW) pool_topk_kernel(Shape sh, Ws ws,
   }
 }
 
-// Mark the batch (indices into the pool, ascending) and record it.
-__device__ void commit_batch(const Shape& sh, const Ws& ws, int p, int round, int bsize, int sel_base,
-                             const int* pool_s, const int* chosen, int32_t* trace_batch) {
-  int* sel = ws.sel + p * ws.s_sel;
-  int* order = ws.order + p * ws.s_ord;
-  int* batch = ws.batch + p * ws.s_bat;
-  for (int k = threadIdx.x; k < bsize; k += blockDim.x) {
-    const int i = pool_s[chosen[k]];
-    sel[i] = round;
-    order[sel_base + k] = i;
-    batch[k] = i;
-  }
-  if (trace_batch) {
-    int32_t* tb = trace_batch + (static_cast<long long>(p) * sh.rounds + round) * sh.b;
-    for (int k = threadIdx.x; k < sh.b; k += blockDim.x) tb[k] = (k < bsize) ? pool_s[chosen[k]] : -1;
-  }
-}
-
-// Ballot-based selection inside one wave.  Keys are held in lanes (KPT per
-// lane); the count of keys >= c is a sum of ballot popcounts, so the
-// count-th largest key value is found by a 32-step bitwise search with no
-// LDS traffic: the largest v with at least `count` keys >= v.
-template <int KPT>
-__device__ __forceinline__ int wave_count_ge(const uint32_t (&k)[KPT], uint32_t c) {
-  int n = 0;
-#pragma unroll
-  for (int q = 0; q < KPT; ++q) n += __popcll(__ballot(k[q] >= c));
-  return n;
-}
-template <int KPT>
-__device__ __forceinline__ uint32_t wave_kth(const uint32_t (&k)[KPT], int count) {
-  uint32_t prefix = 0;
-  for (int bit = 31; bit >= 0; --bit) {
-    const uint32_t cand = prefix | (1u << bit);
-    if (wave_count_ge<KPT>(k, cand) >= count) prefix = cand;
-  }
-  return prefix;
-}
-
-// Wave-level top-b of at most 64 keys (lane = pool position, ascending
-// source index): rank by (key desc, position asc); chosen positions in
-// ascending order.  Called by one whole wave.
-__device__ void wave_topb(const uint32_t* keys, int psize, int bsize, int* chosen) {
-  const int lane = threadIdx.x & 63;
-  const unsigned long long below = (1ull << lane) - 1ull;
-  const uint32_t k[1] = {(lane < psize) ? keys[lane] : 0u};
-  const uint32_t kth = wave_kth<1>(k, bsize);
-  const int quota = bsize - __popcll(__ballot(k[0] > kth));
-  const unsigned long long eqm = __ballot(lane < psize && k[0] == kth);
-  const bool take = lane < psize && (k[0] > kth || (k[0] == kth && __popcll(eqm & below) < quota));
-  const unsigned long long tm = __ballot(take);
-  if (take) chosen[__popcll(tm & below)] = lane;
-}
-
-// Butterfly transpose-reduction: lane l holds v[0..63] (one value per pool
-// position); afterwards v[0] in lane l is the sum over all 64 lanes of the
-// values for position l.  63 exchanges, fixed order.
-template <int O>
-__device__ __forceinline__ void transpose_reduce_step(float* v, int lane) {
-  const bool hi = (lane & O) != 0;
-#pragma unroll
-  for (int k = 0; k < O; ++k) {
-    const float send = hi ? v[k] : v[k + O];
-    const float keep = hi ? v[k + O] : v[k];
-    if constexpr (O < 16) v[k] = keep + xor_lane<O>(send);
-    else v[k] = keep + __shfl_xor(send, O, kWave);
-  }
-}
-__device__ __forceinline__ float transpose_reduce64(float* v, int lane) {
-  transpose_reduce_step<32>(v, lane);
-  transpose_reduce_step<16>(v, lane);
-  transpose_reduce_step<8>(v, lane);
-  transpose_reduce_step<4>(v, lane);
-  transpose_reduce_step<2>(v, lane);
-  transpose_reduce_step<1>(v, lane);
-  return v[0];
-}
 
 // Batch of a small pool from the responsibility block sums (one whole wave):
 // scores summed in block order, top-b by (score desc, index asc).  Leaves
@@ -505,7 +221,7 @@ template <bool kGlobalKeys>
 __global__ void __launch_bounds__(256)
 gains_fused_kernel(Shape sh, Ws ws, int round, int psize, int prev_psize, int prev_bsize, int prev_base,
                    SelOut so) {
-  extern __shared__ float dyn[];      // refreshed coverage [ldM], then LDS keys [N]
+  extern __shared__ __attribute__((aligned(16))) float dyn[];      // refreshed coverage [ldM], then LDS keys [N]
   __shared__ int hist[512], scan[16], bc[2], flag;
   __shared__ int pool_s[64], chosen[64], bidx[64];
   __shared__ __attribute__((aligned(16))) uint32_t bkeys[64];
@@ -795,643 +511,6 @@ colsum_kernel(Shape sh, Ws ws, int round, int psize, int bsize, int sel_base, Se
   commit_batch(sh, ws, p, round, bsize, sel_base, pool, chosen, so.batch);
 }
 
-// ---------------------------------------------------------------------------
-// Persistent selection: every round of a small-pool call in one launch.  The
-// grid is nblk blocks per problem, sized to be co-resident (one block per CU,
-// two for the streamed kernel when it fits twice); every block keeps its own
-// copy of the coverage b_m in LDS and reads the row weights from L2.  A round:
-//   gains  - waves stream the client rows of unselected tokens (round robin
-//            over all waves of the problem) and publish u_i tagged with the
-//            round number
-//   pool   - every block that owns a row chunk (and the last block) waits
-//            for the tagged gains and picks the same pool (identical inputs,
-//            deterministic top-k)
-//   resp   - one block per 64-row chunk, its waves splitting the pool:
-//            responsibility softmax over the pool, per-chunk sums per pool
-//            token, published tagged
-//   batch  - those blocks wait for the tagged chunk sums, add them in chunk
-//            order and pick the same batch; the last block records it and
-//            block 0 publishes its tokens, which are all the other blocks
-//            wait for (with one chunk per block)
-//   cov    - one wave per 64-row chunk: b_m <- max(b_m, max_{j in batch}
-//            Cbar_mj), published tagged; every block waits for the tags and
-//            copies b into LDS
-// In the last round only the last block continues after the batch: it
-// refreshes its own coverage copy, writes the coverage, F(S) and F(V), and
-// the support list (ascending, with each token's slot).
-//
-// Tagged values are double-buffered by round parity, so a buffer is rewritten
-// two rounds after the round that read it.  Along with its coverage rows each
-// block publishes a tagged heartbeat (after it has read everything of the
-// round except the coverage; a block without the pool reads only the batch's
-// tokens, whose slots are rewritten only after every block's gains two
-// rounds on, so it publishes first), and the coverage hand-off waits for
-// every block's heartbeat as well as for the rows.  A block therefore starts round
-// r + 1 only after every block has finished its reads of round r - 1 and
-// earlier, so no value is overwritten before all its readers are done; the
-// ordering rides on a poll that happens anyway, with no barrier and no
-// same-address atomics.  Every wait is
-// bounded: after kSpinLimit polls, or once this block has recorded a timeout,
-// the block records the timeout (device status word) and stops waiting, so
-// every wave always exits.
-constexpr int kSpinLimit = 1 << 18;   // bounded waits (a fraction of a second)
-
-// Marks the call failed (sticky device status bit) after a bounded wait.
-__device__ __forceinline__ void mark_timeout(int* cnt, int* failed) {
-  raise_status(cnt, kStatusSelect);
-  *failed = 1;
-}
-
-// Entry i of the coverage hand-off poll: rows [0, m), then the heartbeats at
-// [ldM, ldM + nblk); the padding rows [m, ldM) are never written and poll
-// row m - 1 instead.
-__device__ __forceinline__ int stage_index(int i, const Shape& sh, int nst) {
-  i = min(i, nst - 1);
-  return (i >= sh.m && i < sh.ldM) ? sh.m - 1 : i;
-}
-
-// Pool of the persistent selection with the keys in registers: thread t
-// takes the gains of its contiguous segment (taken tokens key 0), waiting
-// until each carries this round's tag.
-template <int KPT>
-__device__ __forceinline__ void pool_regs(const Shape& sh, const unsigned long long* tu, unsigned tag,
-                                          const unsigned char* taken, int psize, int* pool_s, int* hist, int* scan,
-                                          int* cnt, int* failed) {
-  const int seg = (sh.N + 255) / 256;
-  const int i0 = threadIdx.x * seg;
-  unsigned long long w[KPT];
-  bool need[KPT];
-#pragma unroll
-  for (int q = 0; q < KPT; ++q) {
-    const int i = min(i0 + q, sh.N - 1);
-    need[q] = q < seg && i0 + q < sh.N && !taken[i];
-    w[q] = ld_dev64(&tu[i]);
-  }
-  for (int spin = 0;; ++spin) {
-    bool pend = false;
-#pragma unroll
-    for (int q = 0; q < KPT; ++q) pend |= need[q] && tag_of(w[q]) != tag;
-    if (!pend || *failed) break;
-    if (spin == kSpinLimit) { mark_timeout(cnt, failed); break; }
-    __builtin_amdgcn_s_sleep(1);
-#pragma unroll
-    for (int q = 0; q < KPT; ++q)
-      if (need[q] && tag_of(w[q]) != tag) w[q] = ld_dev64(&tu[min(i0 + q, sh.N - 1)]);
-  }
-  uint32_t k[KPT];
-#pragma unroll
-  for (int q = 0; q < KPT; ++q) k[q] = need[q] ? score_key(value_of(w[q])) : 0u;
-  block_topk_regs<KPT>(k, seg, psize, pool_s, hist, scan);
-}
-
-// A wave-uniform value the compiler cannot see through (so it is not
-// hoisted out of a loop): through a VGPR and back.
-__device__ __forceinline__ int opaque_uniform(int v) {
-  asm volatile("" : "+v"(v));
-  return __builtin_amdgcn_readfirstlane(v);
-}
-
-// RES: block b owns tokens [8 b, 8 b + 8) (N <= 8 blocks, M <= 256 kResJ) and
-// keeps their weighted client rows alpha_m E[i][m] (Cbar, the product rounded
-// once) in registers for the whole call, wave w holding the rows
-// m = 64 (w + 4 j) + lane, j < kResJ, of all eight tokens; a round's gains
-// then read only the coverage.  Otherwise each wave streams the rows of
-// its tokens (gw, gw + waves, ...) from the caches every round.
-constexpr int kResJ = 14;
-template <bool RES>
-__global__ void __launch_bounds__(256)
-select_persistent_kernel(Shape sh, Params pr, Ws ws, int nblk, SelOut so, int quad) {
-  extern __shared__ float dyn[];
-  // LDS: b_m [ldM] | selected flags [N, padded to 16 bytes] | pool keys [N]
-  //      (only when N exceeds the register top-k); the row weights are read
-  //      from L2 beside the client values they scale, which keeps a block
-  //      small enough for two per CU on the document page
-  float* bl = dyn;
-  unsigned char* taken = reinterpret_cast<unsigned char*>(dyn + sh.ldM);
-  uint32_t* keys = reinterpret_cast<uint32_t*>(taken + ((sh.N + 15) & ~15));
-  __shared__ int hist[768], scan[16], bc[2], failed;
-  __shared__ int pool_s[64], chosen[64], bidx[64];
-  __shared__ __attribute__((aligned(16))) uint32_t bkeys[64];
-  __shared__ float rmu[4][64], rden_s[4][64], red[16];
-  // Cbar of the chunk's rows at the pool's tokens (pool position, row lane),
-  // kept from the responsibilities for the coverage refresh
-  __shared__ float cpool[64][64];
-  const int p = blockIdx.y, blk = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int nwaves = nblk * 4, gw = blk * 4 + wave;
-  const int nchunk = (sh.m + 63) / 64;
-  // the pool and the chunk sums are needed by the blocks that own a row
-  // chunk (responsibilities, coverage) and by the last block (it records the
-  // batch); with one chunk per block the others skip both and wait only for
-  // the batch's tokens, which block 0 publishes after its pick
-  const bool pool_here = nchunk > nblk || blk < nchunk || blk == nblk - 1;
-  const bool pool_pub = nchunk + 1 < nblk;
-  const float* E = ws.E + p * ws.s_E;
-  unsigned long long* tu = ws.tu + p * ws.s_tu;
-  unsigned long long* ts = ws.ts + p * ws.s_ts;
-  unsigned long long* tc = ws.tc + p * ws.s_tc;
-  const float* alpha_g = ws.alpha + p * ws.s_m;
-  int* cnt = ws.cnt + p * ws.s_cnt;
-  {
-    const float* cov0 = ws.cov + p * ws.s_cov;
-    for (int m = tid; m < sh.ldM; m += 256) {
-      // coverage at the first round: zero, or the image seeds' b_m(S_0)
-      bl[m] = sh.nseed > 0 ? cov0[m] : 0.f;
-    }
-  }
-  {
-    const int* sel0 = ws.sel + p * ws.s_sel;
-    for (int i = tid; i < sh.N; i += 256) taken[i] = (sh.nseed > 0 && sel0[i] >= 0) ? 1 : 0;
-  }
-  if (tid == 0) failed = 0;
-  float er[RES ? 8 : 1][RES ? kResJ : 1];
-  if constexpr (RES) {
-    // rows past M and tokens past N hold zeros (clamped loads, then select)
-#pragma unroll
-    for (int j = 0; j < kResJ; ++j) {
-      const int m = 64 * (wave + 4 * j) + lane;
-      const int mc = min(m, sh.m - 1);
-      const float a = alpha_g[mc];
-#pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        const int t = blk * 8 + s;
-        const float v = E[static_cast<long long>(min(t, sh.N - 1)) * sh.ldM + mc];
-        er[s][j] = (m < sh.m && t < sh.N) ? a * v : 0.f;
-      }
-    }
-  }
-  __syncthreads();
-  int selected = sh.nseed;
-  const Shape sh_call = sh;
-  const int tid_call = tid;
-  for (int r = 0; r < sh_call.rounds; ++r) {
-    // Opaque per-round copies of the shape and the thread index: index math
-    // derived from them is redone every round instead of being hoisted out
-    // of the loop and kept live (in spill registers) across all rounds.
-    Shape sh = sh_call;
-    int tid = tid_call;
-    sh.N = opaque_uniform(sh.N);
-    sh.m = opaque_uniform(sh.m);
-    sh.ldM = opaque_uniform(sh.ldM);
-    sh.K = opaque_uniform(sh.K);
-    sh.b = opaque_uniform(sh.b);
-    sh.pool_cap = opaque_uniform(sh.pool_cap);
-    asm volatile("" : "+v"(tid));
-    const int lane = tid & 63, wave = tid >> 6, gw = blk * 4 + wave;
-    const int psize = min(sh.pool_cap, sh.N - selected);
-    const int bsize = min(sh.b, sh.K - selected);
-    const unsigned tag = static_cast<unsigned>(r + 1);
-    unsigned long long* tur = tu + (r & 1) * sh.N;
-    unsigned long long* tsr = ts + (r & 1) * 64LL * nchunk;
-
-    // ---- singleton gains of unselected tokens, two tokens per wave pass with
-    //      all their row loads in flight (or the block's rows held in registers),
-    //      published with this round's tag
-    if constexpr (RES) {
-      // per lane: the partial gains of the eight tokens over its rows
-      // (b_m >= 0, so rows past M add zero); then summed over the lanes and
-      // the four waves, in that order
-      float acc[8];
-#pragma unroll
-      for (int s = 0; s < 8; ++s) acc[s] = 0.f;
-#pragma unroll
-      for (int j = 0; j < kResJ; ++j) {
-        const float b = bl[min(64 * (wave + 4 * j) + lane, sh.ldM - 1)];
-#pragma unroll
-        for (int s = 0; s < 8; ++s) acc[s] += fmaxf(er[s][j] - b, 0.f);
-      }
-      transpose_reduce_step<4>(acc, lane);
-      transpose_reduce_step<2>(acc, lane);
-      transpose_reduce_step<1>(acc, lane);
-      float g = acc[0];             // token lane & 7, summed over 8 lanes
-      g += xor_lane<8>(g);
-      g = add_xor16(g);
-      g = add_xor32(g);
-      if (lane < 8) rmu[wave][lane] = g;
-      __syncthreads();
-      if (tid < 8) {
-        const int t = blk * 8 + tid;
-        const float g = ((rmu[0][tid] + rmu[1][tid]) + rmu[2][tid]) + rmu[3][tid];
-        if (t < sh.N && !taken[t]) st_dev64(&tur[t], tag_value(tag, g));
-        if (so.gains && t < sh.N)
-          so.gains[(static_cast<long long>(p) * sh.rounds + r) * sh.N + t] = taken[t] ? 0.f : g;
-      }
-    } else if (quad) {
-      // one block per CU: four tokens per wave pass, all their row loads in
-      // flight together (each token's sum is formed exactly as in the
-      // two-token loop below)
-      for (int i0 = gw; i0 < sh.N; i0 += 4 * nwaves) {
-        int it[4];
-        bool ok[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          it[k] = i0 + k * nwaves;
-          ok[k] = it[k] < sh.N && taken[min(it[k], sh.N - 1)] == 0;
-        }
-        float* gout = so.gains ? so.gains + (static_cast<long long>(p) * sh.rounds + r) * sh.N : nullptr;
-        if (!(ok[0] || ok[1] || ok[2] || ok[3])) {
-          if (gout && lane == 0)
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-              if (it[k] < sh.N) gout[it[k]] = 0.f;
-          continue;
-        }
-        // a token that needs no gain re-reads a needed one's row (cache hits)
-        const int any = ok[0] ? it[0] : ok[1] ? it[1] : ok[2] ? it[2] : it[3];
-        const float* c[4];
-        float acc[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          c[k] = E + static_cast<long long>(ok[k] ? it[k] : any) * sh.ldM;
-          acc[k] = 0.f;
-        }
-#pragma unroll 4
-        for (int m = lane * 4; m < sh.m; m += 256) {
-          const float4 a = *reinterpret_cast<const float4*>(alpha_g + m);
-          const float4 b = *reinterpret_cast<const float4*>(bl + m);
-          float4 v[4];
-#pragma unroll
-          for (int k = 0; k < 4; ++k) v[k] = *reinterpret_cast<const float4*>(c[k] + m);
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            acc[k] += fmaxf(a.x * v[k].x - b.x, 0.f); acc[k] += fmaxf(a.y * v[k].y - b.y, 0.f);
-            acc[k] += fmaxf(a.z * v[k].z - b.z, 0.f); acc[k] += fmaxf(a.w * v[k].w - b.w, 0.f);
-          }
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) acc[k] = wave_sum(acc[k]);
-        if (lane == 0)
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            if (ok[k]) st_dev64(&tur[it[k]], tag_value(tag, acc[k]));
-            if (gout && it[k] < sh.N) gout[it[k]] = ok[k] ? acc[k] : 0.f;
-          }
-      }
-    } else
-    for (int i0 = gw; i0 < sh.N; i0 += 2 * nwaves) {
-      const int i1 = i0 + nwaves;
-      const bool ok0 = taken[i0] == 0;
-      const bool ok1 = i1 < sh.N && taken[min(i1, sh.N - 1)] == 0;
-      float* gout = so.gains ? so.gains + (static_cast<long long>(p) * sh.rounds + r) * sh.N : nullptr;
-      if (!ok0 && !ok1) {
-        if (gout && lane == 0) {
-          gout[i0] = 0.f;
-          if (i1 < sh.N) gout[i1] = 0.f;
-        }
-        continue;
-      }
-      // a token that needs no gain re-reads the other one's row (cache hits)
-      const float* c0 = E + static_cast<long long>(ok0 ? i0 : i1) * sh.ldM;
-      const float* c1 = E + static_cast<long long>(ok1 ? i1 : i0) * sh.ldM;
-      float a0 = 0.f, a1 = 0.f;
-#pragma unroll 4
-      for (int m = lane * 4; m < sh.m; m += 256) {
-        const float4 a = *reinterpret_cast<const float4*>(alpha_g + m);
-        const float4 b = *reinterpret_cast<const float4*>(bl + m);
-        const float4 v0 = *reinterpret_cast<const float4*>(c0 + m);
-        const float4 v1 = *reinterpret_cast<const float4*>(c1 + m);
-        a0 += fmaxf(a.x * v0.x - b.x, 0.f); a0 += fmaxf(a.y * v0.y - b.y, 0.f);
-        a0 += fmaxf(a.z * v0.z - b.z, 0.f); a0 += fmaxf(a.w * v0.w - b.w, 0.f);
-        a1 += fmaxf(a.x * v1.x - b.x, 0.f); a1 += fmaxf(a.y * v1.y - b.y, 0.f);
-        a1 += fmaxf(a.z * v1.z - b.z, 0.f); a1 += fmaxf(a.w * v1.w - b.w, 0.f);
-      }
-      a0 = wave_sum(a0);
-      a1 = wave_sum(a1);
-      if (lane == 0) {
-        if (ok0) st_dev64(&tur[i0], tag_value(tag, a0));
-        if (ok1) st_dev64(&tur[i1], tag_value(tag, a1));
-        if (gout) {
-          gout[i0] = ok0 ? a0 : 0.f;
-          if (i1 < sh.N) gout[i1] = ok1 ? a1 : 0.f;
-        }
-      }
-    }
-
-    // ---- the pool, identical in every block that needs it (waits for this
-    //      round's gains)
-    // the batch's tokens, published by block 0 for the blocks without the pool
-    unsigned long long* tpr = ts + 128LL * nchunk + (r & 1) * 64;
-    if (pool_here) {
-    if constexpr (RES) {
-      if (sh.N <= 256 * 6)
-        pool_regs<6>(sh, tur, tag, taken, psize, pool_s, hist, scan, cnt, &failed);
-      else
-        pool_regs<8>(sh, tur, tag, taken, psize, pool_s, hist, scan, cnt, &failed);
-    } else if (sh.N <= 256 * 8)
-      pool_regs<8>(sh, tur, tag, taken, psize, pool_s, hist, scan, cnt, &failed);
-    else if (sh.N <= 256 * 16)
-      pool_regs<16>(sh, tur, tag, taken, psize, pool_s, hist, scan, cnt, &failed);
-    else {
-      for (int base = 0; base < sh.N; base += 256 * 16) {
-        unsigned long long w[16];
-        bool need[16];
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-          const int i = base + q * 256 + tid;
-          need[q] = i < sh.N && !taken[min(i, sh.N - 1)];
-          w[q] = ld_dev64(&tur[min(i, sh.N - 1)]);
-        }
-        for (int spin = 0;; ++spin) {
-          bool pend = false;
-#pragma unroll
-          for (int q = 0; q < 16; ++q) pend |= need[q] && tag_of(w[q]) != tag;
-          if (!pend || failed) break;
-          if (spin == kSpinLimit) { mark_timeout(cnt, &failed); break; }
-          __builtin_amdgcn_s_sleep(1);
-#pragma unroll
-          for (int q = 0; q < 16; ++q)
-            if (need[q] && tag_of(w[q]) != tag) w[q] = ld_dev64(&tur[min(base + q * 256 + tid, sh.N - 1)]);
-        }
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-          const int i = base + q * 256 + tid;
-          if (i < sh.N) keys[i] = need[q] ? score_key(value_of(w[q])) : 0u;
-        }
-      }
-      __syncthreads();
-      block_topk256(keys, sh.N, psize, pool_s, hist, scan, bc);
-    }
-    if constexpr (!RES) {
-      // clamp to valid rows (defensive) and pad past psize with a valid row,
-      // masked below (the register top-k pads with row 0 itself)
-      int pv = 0;
-      if (tid < 64) pv = min(max(pool_s[tid < psize ? tid : 0], 0), sh.N - 1);
-      __syncthreads();
-      if (tid < 64) pool_s[tid] = pv;
-      __syncthreads();
-    }
-    }
-    if (blk == nblk - 1 && so.pool) {
-      int32_t* tp = so.pool + (static_cast<long long>(p) * sh.rounds + r) * sh.pool_cap;
-      for (int j = tid; j < sh.pool_cap; j += 256) tp[j] = (j < psize) ? pool_s[j] : -1;
-    }
-
-    // ---- responsibilities: one block per 64-row chunk (lane = client row),
-    //      its four waves split the pool positions 16 apiece; the per-chunk
-    //      sums are published with this round's tag
-    for (int c = blk; c < nchunk; c += nblk) {
-      const int m = c * 64 + lane;
-      const bool row_ok = m < sh.m;
-      const int mc = row_ok ? m : 0;
-      const float a = row_ok ? alpha_g[mc] : 0.f;
-      const float b = bl[mc];
-      const int j0 = wave * 16;
-      float v[16];
-#pragma unroll
-      for (int j = 0; j < 16; ++j) v[j] = E[static_cast<long long>(pool_s[j0 + j]) * sh.ldM + mc];
-      float mu = 0.f;
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const float cb = a * v[j];
-        cpool[j0 + j][lane] = cb;
-        const float rr = (j0 + j < psize) ? fmaxf(cb - b, 0.f) : 0.f;
-        v[j] = rr;
-        mu = fmaxf(mu, rr);
-      }
-      rmu[wave][lane] = mu;
-      __syncthreads();
-      mu = fmaxf(fmaxf(rmu[0][lane], rmu[1][lane]), fmaxf(rmu[2][lane], rmu[3][lane]));
-      const float inv = mu > 0.f ? 1.f / (pr.tau_r * mu + pr.resp_eps) : 0.f;
-      const float zmax = mu * inv;
-      float den = 0.f;
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const float ex = (j0 + j < psize) ? __expf(v[j] * inv - zmax) : 0.f;
-        den += ex;
-        v[j] *= ex;    // rho numerator times R; scaled by 1/den below
-      }
-      rden_s[wave][lane] = den;
-      __syncthreads();
-      den = ((rden_s[0][lane] + rden_s[1][lane]) + rden_s[2][lane]) + rden_s[3][lane];
-      const float rden = mu > 0.f ? 1.f / den : 0.f;
-#pragma unroll
-      for (int j = 0; j < 16; ++j) v[j] *= rden;
-      // sum over the 64 rows per pool position: butterfly inside 16-lane
-      // groups, then across the four groups
-      transpose_reduce_step<8>(v, lane);
-      transpose_reduce_step<4>(v, lane);
-      transpose_reduce_step<2>(v, lane);
-      transpose_reduce_step<1>(v, lane);
-      float tot = v[0];
-      tot = add_xor16(tot);
-      tot = add_xor32(tot);
-      if (lane < 16) st_dev64(&tsr[static_cast<long long>(c) * 64 + j0 + lane], tag_value(tag, tot));
-      __syncthreads();   // rmu / rden_s are reused by the next chunk
-    }
-
-    // ---- the batch, identical in every block with the pool: each wave waits
-    //      for the tagged sums of a quarter of the chunks (16 loads in
-    //      flight) and adds them in chunk order; the quarters are added in
-    //      wave order.  The other blocks wait for the batch's tokens alone.
-    if (!pool_here) {
-      // nothing left for these blocks in the last round
-      if (r + 1 == sh.rounds) break;
-      // they read nothing else of this round (the batch's slots are
-      // rewritten two rounds on, after every block's gains of that round),
-      // so their heartbeat goes out before the wait
-      if (tid == 0) st_dev64(&tc[(r & 1) * (sh.ldM + kMaxPersist) + sh.ldM + blk], tag_value(tag, 0.f));
-      if (tid < 16) {
-        unsigned long long bw = ld_dev64(&tpr[tid]);
-        for (int spin = 0; tag_of(bw) != tag && !failed; ++spin) {
-          if (spin == kSpinLimit) { mark_timeout(cnt, &failed); break; }
-          __builtin_amdgcn_s_sleep(1);
-          bw = ld_dev64(&tpr[tid]);
-        }
-        bidx[tid] = min(max(__float_as_int(value_of(bw)), 0), sh.N - 1);
-      }
-      __syncthreads();
-    } else {
-    {
-      const int per = (nchunk + 3) / 4;
-      const int c_end = min(nchunk, (wave + 1) * per);
-      float s = 0.f;
-      for (int c0 = wave * per; c0 < c_end; c0 += 16) {
-        unsigned long long w[16];
-#pragma unroll
-        for (int q = 0; q < 16; ++q) w[q] = ld_dev64(&tsr[static_cast<long long>(min(c0 + q, c_end - 1)) * 64 + lane]);
-        for (int spin = 0;; ++spin) {
-          bool pend = false;
-#pragma unroll
-          for (int q = 0; q < 16; ++q) pend |= tag_of(w[q]) != tag;
-          if (!pend || failed) break;
-          if (spin == kSpinLimit) { mark_timeout(cnt, &failed); break; }
-          __builtin_amdgcn_s_sleep(1);
-#pragma unroll
-          for (int q = 0; q < 16; ++q)
-            if (tag_of(w[q]) != tag) w[q] = ld_dev64(&tsr[static_cast<long long>(min(c0 + q, c_end - 1)) * 64 + lane]);
-        }
-#pragma unroll
-        for (int q = 0; q < 16; ++q)
-          if (c0 + q < c_end) s += value_of(w[q]);
-      }
-      rmu[wave][lane] = s;   // free: the responsibility loop ended with a barrier
-    }
-    __syncthreads();
-    if (wave == 0) {
-      const float s = ((rmu[0][lane] + rmu[1][lane]) + rmu[2][lane]) + rmu[3][lane];
-      if (blk == nblk - 1 && so.scores && lane < sh.pool_cap)
-        so.scores[(static_cast<long long>(p) * sh.rounds + r) * sh.pool_cap + lane] = lane < psize ? s : 0.f;
-      bkeys[lane] = score_key(s);
-      __builtin_amdgcn_wave_barrier();
-      wave_topb(bkeys, psize, bsize, chosen);
-      __builtin_amdgcn_wave_barrier();
-      if (lane < bsize) bidx[lane] = pool_s[chosen[lane]];
-      __builtin_amdgcn_wave_barrier();
-      if (pool_pub && blk == 0 && lane < 16)
-        st_dev64(&tpr[lane], tag_value(tag, __int_as_float(lane < bsize ? bidx[lane] : 0)));
-    }
-    __syncthreads();
-    }
-    const bool last = r + 1 == sh.rounds;
-    // the last block records the batch (and alone finishes the last round)
-    if (blk == nblk - 1) commit_batch(sh, ws, p, r, bsize, selected, pool_s, chosen, so.batch);
-    else if (last) break;
-    if (tid < bsize) taken[bidx[tid]] = 1;
-    if (!last) {
-      // ---- coverage refresh with the batch, published with this round's
-      //      tag: with one chunk per block, by the chunk's responsibility
-      //      block (its pool columns, the batch among them, were just read
-      //      here, so the loads hit this XCD's L2), wave w taking batch
-      //      entries w, w + 4, ...; otherwise one wave per 64-row chunk
-      unsigned long long* tcr = tc + (r & 1) * (sh.ldM + kMaxPersist);
-      if (nchunk <= nblk && bsize <= 16) {
-        if (blk < nchunk) {
-          const int m = blk * 64 + lane;
-          const int mc = min(m, sh.m - 1);
-          // the pool holds at most 64 = 4 b entries here, so b <= 16: four
-          // batch entries per wave, their Cbar values kept in LDS by this
-          // block's responsibility pass over the same rows
-          float cm = bl[mc];
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (wave + 4 * q < bsize) cm = fmaxf(cm, cpool[chosen[wave + 4 * q]][lane]);
-          rmu[wave][lane] = cm;   // free: last read before the barrier after the batch
-          __syncthreads();
-          if (wave == 0 && m < sh.m)
-            st_dev64(&tcr[m], tag_value(tag, fmaxf(fmaxf(rmu[0][lane], rmu[1][lane]), fmaxf(rmu[2][lane], rmu[3][lane]))));
-        }
-      } else
-      for (int c = gw; c < nchunk; c += nwaves) {
-        const int m = c * 64 + lane;
-        const int mc = min(m, sh.m - 1);
-        const float a = alpha_g[mc];
-        float cm = bl[mc];
-        for (int k0 = 0; k0 < bsize; k0 += 16) {
-          float v[16];
-#pragma unroll
-          for (int q = 0; q < 16; ++q) v[q] = E[static_cast<long long>(bidx[min(k0 + q, bsize - 1)]) * sh.ldM + mc];
-#pragma unroll
-          for (int q = 0; q < 16; ++q) cm = fmaxf(cm, a * v[q]);
-        }
-        if (m < sh.m) st_dev64(&tcr[m], tag_value(tag, cm));
-      }
-      // this block's heartbeat: it has read everything of earlier rounds
-      if (pool_here && tid == 0) st_dev64(&tcr[sh.ldM + blk], tag_value(tag, 0.f));
-      // ---- every block copies the refreshed coverage into LDS, waiting for
-      //      the tags and for every block's heartbeat
-      const int nst = sh.ldM + nblk;
-      for (int m0 = 0; m0 < nst; m0 += 256 * 16) {
-        unsigned long long w[16];
-#pragma unroll
-        for (int q = 0; q < 16; ++q) w[q] = ld_dev64(&tcr[stage_index(m0 + q * 256 + tid, sh, nst)]);
-        for (int spin = 0;; ++spin) {
-          bool pend = false;
-#pragma unroll
-          for (int q = 0; q < 16; ++q) pend |= tag_of(w[q]) != tag;
-          if (!pend || failed) break;
-          if (spin == kSpinLimit) { mark_timeout(cnt, &failed); break; }
-          __builtin_amdgcn_s_sleep(1);
-#pragma unroll
-          for (int q = 0; q < 16; ++q)
-            if (tag_of(w[q]) != tag) w[q] = ld_dev64(&tcr[stage_index(m0 + q * 256 + tid, sh, nst)]);
-        }
-#pragma unroll
-        for (int q = 0; q < 16; ++q)
-          if (m0 + q * 256 + tid < sh.m) bl[m0 + q * 256 + tid] = value_of(w[q]);
-      }
-      __syncthreads();
-      selected += bsize;
-      continue;
-    }
-
-    // ---- the last round (last block only): coverage refresh of the LDS copy
-    //      with two row groups per trip, 16 batch rows each, all loads in flight
-    for (int m0 = tid * 4; m0 < sh.m; m0 += 2048) {
-      float4 c[2];
-      c[0] = c[1] = make_float4(0.f, 0.f, 0.f, 0.f);
-      for (int k0 = 0; k0 < bsize; k0 += 16) {
-        // indices past the batch repeat its last row: a maximum is unchanged
-        float4 v[2][16];
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-          for (int q = 0; q < 16; ++q)
-            v[h][q] = *reinterpret_cast<const float4*>(E + static_cast<long long>(bidx[min(k0 + q, bsize - 1)]) * sh.ldM +
-                                                       min(m0 + h * 1024, sh.ldM - 4));
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-          for (int q = 0; q < 16; ++q) {
-            c[h].x = fmaxf(c[h].x, v[h][q].x); c[h].y = fmaxf(c[h].y, v[h][q].y);
-            c[h].z = fmaxf(c[h].z, v[h][q].z); c[h].w = fmaxf(c[h].w, v[h][q].w);
-          }
-      }
-      // alpha_m >= 0, so alpha_m max_j Et[j][m] = max_j Cbar_mj exactly
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int m = m0 + h * 1024;
-        if (m < sh.m) {
-          const float4 a = *reinterpret_cast<const float4*>(alpha_g + m);
-          float4 b = *reinterpret_cast<const float4*>(bl + m);
-          b.x = fmaxf(b.x, a.x * c[h].x); b.y = fmaxf(b.y, a.y * c[h].y);
-          b.z = fmaxf(b.z, a.z * c[h].z); b.w = fmaxf(b.w, a.w * c[h].w);
-          *reinterpret_cast<float4*>(bl + m) = b;
-        }
-      }
-    }
-    selected += bsize;
-    __syncthreads();
-    if (last) {
-      // the last block: the coverage, F(S) = sum_m b_m and F(V) = sum_m
-      // max_i Cbar_mi, then the support list in ascending source order with
-      // each token's slot
-      float* cov = ws.cov + p * ws.s_cov;
-      const float* peak = ws.peak + p * ws.s_m;
-      float fs = 0.f, fv = 0.f;
-      for (int m = tid; m < sh.m; m += 256) {
-        cov[m] = bl[m];
-        fs += bl[m];
-        fv += peak[m];
-      }
-      fs = block_sum(fs, red);
-      fv = block_sum(fv, red);
-      int* sup = ws.sup + p * ws.s_sup;
-      int* slot = ws.slot + p * ws.s_slot;
-      int base = 0;
-      for (int b0 = 0; b0 < sh.N; b0 += 256) {
-        const int i = b0 + tid;
-        const int f = (i < sh.N && taken[i]) ? 1 : 0;
-        int tot;
-        const int pos = base + block_exclusive_scan(f, scan, &tot);
-        if (i < sh.N) {
-          slot[i] = f ? pos : -1;
-          if (f) sup[pos] = i;
-        }
-        base += tot;
-      }
-      if (tid == 0) {
-        float* st = ws.stats + p * ws.s_st;
-        st[2] = fs;
-        st[3] = fv;
-        st[4] = static_cast<float>(sh.K);
-        st[5] = static_cast<float>(sh.rounds);
-        st[6] = static_cast<float>(sh.m);
-        st[7] = static_cast<float>(sh.N - sh.K);
-      }
-      break;
-    }
-  }
-}
 
 // F(S) = sum_m b_m(S) and F(V) = sum_m max_i Cbar_mi via per-block partials
 // reduced in order by the last block.
@@ -1474,51 +553,116 @@ static void launch_cov(const Shape& sh, const Ws& ws, int nb, hipStream_t st) {
                      st, sh, ws, nb);
 }
 
-// Blocks per problem for the persistent selection, or 0 when the call does
-// not qualify (large pools, keys beyond LDS).  The grid never exceeds what
-// the device holds at once (one block per CU, checked against the kernel's
-// occupancy), so on a device not shared with other work every block is
-// resident from the start.  The launch is an ordinary one: a cooperative
-// launch costs a cross-queue synchronisation on each side of the kernel, and
-// the bounded barrier waits already turn a block that never becomes resident
-// (a device saturated by foreign work) into a reported timeout rather than a
-// hang.
-static const void* persistent_fn(int res) {
-  return res ? reinterpret_cast<const void*>(select_persistent_kernel<true>)
-             : reinterpret_cast<const void*>(select_persistent_kernel<false>);
-}
+// Variants of the persistent selection.  The grid never exceeds what the
+// device holds at once (checked against the kernel's occupancy), so on a
+// device not shared with other work every block is resident from the start.
+// The launch is an ordinary one: a cooperative launch costs a cross-queue
+// synchronisation on each side of the kernel, and the bounded waits already
+// turn a block that never becomes resident (a device saturated by foreign
+// work) into a reported timeout rather than a hang.
+struct SelVariant {
+  const void* fn;
+  int J, R;            // rows / 256 and tokens per wave held in registers (0: none)
+  int lds;             // dynamic LDS the occupancy below was asked for (-1: not yet)
+  int per_cu;
+};
+enum { kSelStream, kSelWide, kSelSplit, kSelHold };   // g_sel: hold variants by J, then R
+static SelVariant g_sel[] = {
+    {reinterpret_cast<const void*>(select_stream_kernel), 0, 0, -1, 0},
+    {reinterpret_cast<const void*>(select_wide_kernel), 0, 0, -1, 0},
+    {reinterpret_cast<const void*>(select_split_kernel), 0, 0, -1, 0},
+#define GMC_HOLD(J, R) {reinterpret_cast<const void*>(select_hold_kernel<J, R>), J, R, -1, 0},
+    GMC_HOLD(4, 5) GMC_HOLD(8, 5) GMC_HOLD(14, 3) GMC_HOLD(14, 5) GMC_HOLD(20, 2) GMC_HOLD(20, 3) GMC_HOLD(24, 3)
+    GMC_HOLD(28, 2) GMC_HOLD(32, 2) GMC_HOLD(36, 2) GMC_HOLD(48, 1)
+#undef GMC_HOLD
+};
+static std::mutex g_sel_mu;   // the static-scratch entry point runs beside the context's calls
+static int g_n_cu = -1, g_lds_max = 0;
 
-static int g_n_cu = -1;   // compute units of the current device (0: unknown)
-
-static int persistent_blocks(const Shape& sh, size_t lds, int res) {
-  static int lds_max = 0, lds_set[2] = {64 * 1024, 64 * 1024};
-  int& n_cu = g_n_cu;
-  if (n_cu < 0) {
+// Blocks of a variant that one CU holds at once, 0 if none (g_sel_mu held).
+static int variant_per_cu(SelVariant& v, size_t lds) {
+  if (g_n_cu < 0) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
-      n_cu = 0;
+        hipDeviceGetAttribute(&g_n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipDeviceGetAttribute(&g_lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
+      g_n_cu = 0;
   }
-  if (n_cu <= 0 || sh.pool_cap > 64 || sh.N > kLdsKeys || lds > static_cast<size_t>(lds_max)) return 0;
-  const int v = res ? 1 : 0;
-  if (static_cast<int>(lds) > lds_set[v]) {
+  if (g_n_cu <= 0 || lds > static_cast<size_t>(g_lds_max)) return 0;
+  if (v.lds != static_cast<int>(lds)) {
+    v.lds = static_cast<int>(lds);
+    v.per_cu = 0;
+    int n = 0;
     // dynamic LDS above 64 KB has to be granted to the kernel first
-    if (hipFuncSetAttribute(persistent_fn(res), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            static_cast<int>(lds)) != hipSuccess)
-      return 0;
-    lds_set[v] = static_cast<int>(lds);
+    if ((lds <= 64 * 1024 ||
+         hipFuncSetAttribute(v.fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)) == hipSuccess) &&
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, v.fn, 256, lds) == hipSuccess)
+      v.per_cu = n;
+    else
+      (void)hipGetLastError();   // too much LDS beside the static arrays: another variant is taken
   }
-  int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, persistent_fn(res), 256, lds) != hipSuccess || per_cu < 1)
-    return 0;
-  // about two gain tokens per wave; one block per CU, or two when the
-  // streamed (non-resident) kernel fits twice, which doubles the waves that
-  // stream the client rows
-  const int cap = (res ? 1 : std::min(per_cu, 2)) * n_cu / sh.B;
+  return v.per_cu;
+}
+
+struct SelPlan {
+  const SelVariant* v = nullptr;   // null: the call does not qualify
+  int nblk = 0;                    // blocks per problem
+  size_t lds = 0;
+};
+
+// The persistent variant of a call: not with large pools or keys beyond LDS.
+// Per token the row-split kernel forms the sums in its own order; held and
+// streamed rows share another, so a shape keeps one result whichever of them
+// it takes.
+static SelPlan select_plan(const Shape& sh) {
+  SelPlan pl;
+  if (sh.pool_cap > 64 || sh.N > kLdsKeys) return pl;
+  std::lock_guard<std::mutex> lk(g_sel_mu);
+  // LDS besides the static arrays (see select_rounds)
+  auto lds_of = [&](const SelVariant& v, int blocks) {
+    const size_t groups = v.R ? v.J : (sh.m + 255) / 256;
+    const size_t rows = &v == &g_sel[kSelSplit] ? sh.ldM : &v == &g_sel[kSelWide] ? 256 * groups : 512 * groups;
+    return 4 * (rows + static_cast<size_t>(sh.N + 15) / 16 * 4 + static_cast<size_t>((sh.N + blocks - 1) / blocks) +
+                (sh.N > 256 * 16 ? sh.N : 0));
+  };
+  // blocks with at least one token each
+  auto full = [&](int blocks) { const int t = (sh.N + blocks - 1) / blocks; return (sh.N + t - 1) / t; };
+  auto take = [&](SelVariant& v, int blocks, int per_cu) {
+    const size_t lds = lds_of(v, blocks);
+    if (min(variant_per_cu(v, lds), per_cu) * g_n_cu < blocks * sh.B) return false;
+    pl.v = &v;
+    pl.nblk = blocks;
+    pl.lds = lds;
+    return true;
+  };
+  if (variant_per_cu(g_sel[kSelStream], 0) < 1) return pl;
+  // about two gain tokens per wave
   const int want = max((sh.N + 7) / 8, ((sh.m + 63) / 64 + 3) / 4);
-  const int nblk = min(min(cap, want), kMaxPersist);
-  return nblk >= 1 ? nblk : 0;
+  const int one = min(min(g_n_cu / sh.B, want), kMaxPersist);   // one block per CU
+  if (one >= 1 && sh.N <= 8 * one && sh.m <= 256 * kResJ && take(g_sel[kSelSplit], (sh.N + 7) / 8, 1)) return pl;
+  if (one >= 1) {
+    // rows in registers: the narrowest variant the rows fit, of those the
+    // fewest tokens per wave that cover the block's, else the most.  Held
+    // rows win wherever they were measured, from one image (M = 6944: 460
+    // against 496 us per call; M = 4692, N = 2580: 767 against 915; the
+    // document page 1673 against 1994) to sixteen (1271 against 1296, 31 % of
+    // the tokens held).
+    const int nblk = full(one), tokens = ((sh.N + nblk - 1) / nblk + 3) / 4;
+    SelVariant* best = nullptr;
+    for (int i = kSelHold; i < static_cast<int>(sizeof(g_sel) / sizeof(g_sel[0])); ++i) {
+      SelVariant& v = g_sel[i];
+      if (256 * v.J < sh.m || (best && (v.J > best->J || best->R >= tokens))) continue;
+      best = &v;
+    }
+    if (best && take(*best, nblk, 1)) return pl;
+  }
+  // streamed: two blocks per CU where they fit, twice the waves in flight
+  for (const int i : {kSelStream, kSelWide})
+    for (int per = 2; per >= 1; --per) {
+      const int blocks = min(min(per * g_n_cu / sh.B, want), kMaxPersist);
+      if (blocks >= 1 && take(g_sel[i], full(blocks), per)) return pl;
+    }
+  return pl;
 }
 
 hipError_t launch_selection(const Shape& sh, const Params& pr, const Ws& ws, const SelOut& so, hipStream_t st,
@@ -1532,31 +676,18 @@ hipError_t launch_selection(const Shape& sh, const Params& pr, const Ws& ws, con
     timer_mark(kStObjective, false, st);
     return hipGetLastError();
   }
-  {
-    const size_t lds = static_cast<size_t>(sh.ldM) * sizeof(float) +
-                       ((static_cast<size_t>(sh.N) + 15) & ~static_cast<size_t>(15)) +
-                       (sh.N > 256 * 16 ? static_cast<size_t>(sh.N) * sizeof(uint32_t) : 0);
-    int nblk = persistent_blocks(sh, lds, 0);
-    // the blocks' client rows held in registers when each block owns at
-    // most eight tokens and the rows are short enough
-    const bool resident = nblk > 0 && sh.N <= 8 * nblk && sh.m <= 256 * kResJ &&
-                          persistent_blocks(sh, lds, 1) == nblk;
-    if (nblk > 0) {
-      timer_mark(kStSelect, true, st);
-      // the streamed gains take four tokens per wave pass when the grid has
-      // one block per CU (registers to spare); with two per CU the two-token
-      // loop measured faster
-      const int quad = !resident && g_n_cu > 0 && nblk * sh.B <= g_n_cu;
-      if (resident)
-        hipLaunchKernelGGL(select_persistent_kernel<true>, dim3(nblk, sh.B), dim3(256), lds, st, sh, pr, ws,
-                           nblk, so, 0);
-      else
-        hipLaunchKernelGGL(select_persistent_kernel<false>, dim3(nblk, sh.B), dim3(256), lds, st, sh, pr, ws, nblk,
-                           so, quad);
-      timer_mark(kStSelect, false, st);
-      *support_ready = true;
-      return hipGetLastError();
-    }
+  if (const SelPlan pl = select_plan(sh); pl.v) {
+    timer_mark(kStSelect, true, st);
+    Shape a0 = sh;
+    Params a1 = pr;
+    Ws a2 = ws;
+    int a3 = pl.nblk;
+    SelOut a4 = so;
+    void* args[] = {&a0, &a1, &a2, &a3, &a4};
+    const hipError_t e = hipLaunchKernel(pl.v->fn, dim3(pl.nblk, sh.B), dim3(256), args, pl.lds, st);
+    timer_mark(kStSelect, false, st);
+    *support_ready = true;
+    return e != hipSuccess ? e : hipGetLastError();
   }
   const bool global_keys = sh.N > kLdsKeys;
   const size_t key_lds = global_keys ? 0 : static_cast<size_t>(sh.N) * sizeof(uint32_t);
