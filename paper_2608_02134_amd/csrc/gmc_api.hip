@@ -919,14 +919,16 @@ int gmc_audit_message(int64_t B, int64_t N, int64_t T, int64_t K, const void* te
   long long off = 0;
   auto take = [&](long long elems) { const long long o = off; off += (elems + 63) / 64 * 64; return o; };
   const long long oA = take(B * N * mg1), oY = take(B * mg1 * s.dh), oL = take(B * mg1), oM = take(B * K * mg1);
-  const long long oO = take(B * (K + 1)), oMem = take(B * N), oC = take(B * K), oR = take(B * mg1 * kAuditRow);
+  const long long oR = take(B * mg1 * kAuditRow);
+  // carrier lists of B (K + 1), B N and B K words belong to the requirement
+  // (what a context accepts does not depend on how the lists are formed)
+  (void)take(B * (K + 1)), (void)take(B * N), (void)take(B * K);
   const long long cap = c.ws.s_E * c.cap.B;
   if (off > cap)
     return fail(GMC_ERR_CAPACITY, "gmc_audit_message: needs %lld floats of scratch, the client-matrix buffer holds %lld",
                 off, cap);
   float* base = c.ws.E;
-  AudWs aw{base + oA, base + oY, base + oL, base + oM, reinterpret_cast<int*>(base + oO),
-           reinterpret_cast<int*>(base + oMem), reinterpret_cast<int*>(base + oC), base + oR};
+  AudWs aw{base + oA, base + oY, base + oL, base + oM, base + oR};
   hipError_t err = hipSetDevice(c.device);
   hipStream_t st = c.stream;
   if (err == hipSuccess && c.order_stream && st != c.order_stream) {

@@ -78,9 +78,6 @@ struct AudWs {
   float* Y;      // [B][mg1][dh]  Full messages
   float* lse;    // [B][mg1]      Full log-sum-exp (with the nonvisual part)
   float* Mt;     // [B][K][mg1]   grouped Full mass, carrier-major
-  int* off;      // [B][K + 1]    member list offsets per carrier
-  int* mem;      // [B][N]        members, ascending within a carrier
-  int* cur;      // [B][K]        placement cursors
   float* rowst;  // [B][mg1][kAuditRow] per-client statistics
 };
 
