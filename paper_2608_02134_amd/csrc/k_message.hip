@@ -152,12 +152,28 @@ __global__ void __launch_bounds__(256) sigma_ell_kernel(Shape sh, Params pr, Ws 
     const float* zp = ws.zp + static_cast<long long>(p) * ksplit * sh.N * sh.hr +
                       static_cast<long long>(ic) * sh.hr + h * sh.r;
     const long long sstride = static_cast<long long>(sh.N) * sh.hr;
+    // r = 4: a head's coordinates are one aligned 16-byte run.  Lanes are a
+    // token (hq r floats) apart, so requests bound this kernel and a run is a
+    // quarter of them: 16 problems of 1296 tokens 93 -> 54 us, a clip of 16384
+    // tokens 27 -> 14, 256 tokens 4.9 -> 3.4.  Other r keep single loads.
     float v[kProbeSplit][kMaxProbe];
+    const bool run4 = sh.r == 4;
+    if (run4) {
 #pragma unroll
-    for (int s = 0; s < kProbeSplit; ++s)
+      for (int s = 0; s < kProbeSplit; ++s) {
+        const float4 x = s < ksplit ? *reinterpret_cast<const float4*>(zp + s * sstride) : make_float4(0.f, 0.f, 0.f, 0.f);
+        v[s][0] = x.x; v[s][1] = x.y; v[s][2] = x.z; v[s][3] = x.w;
 #pragma unroll
-      for (int c = 0; c < kMaxProbe; ++c)
-        v[s][c] = (s < ksplit && c < sh.r) ? zp[s * sstride + c] : 0.f;
+        for (int c = 4; c < kMaxProbe; ++c) v[s][c] = 0.f;
+      }
+    } else {
+#pragma unroll
+      for (int s = 0; s < kProbeSplit; ++s)
+#pragma unroll
+        for (int c = 0; c < kMaxProbe; ++c)
+          v[s][c] = (s < ksplit && c < sh.r) ? zp[s * sstride + c] : 0.f;
+    }
+    float zo[kMaxProbe];
     const float rs = rsqrtf(ws.n2[p * ws.s_n + ic] / static_cast<float>(sh.d) + pr.rms_eps);
     float q = 0.f;
     float* z = ws.z + p * ws.s_z + static_cast<long long>(ic) * sh.hr + h * sh.r;
@@ -167,9 +183,11 @@ __global__ void __launch_bounds__(256) sigma_ell_kernel(Shape sh, Params pr, Ws 
         const float zs = (((v[0][c] + v[1][c]) + v[2][c]) + v[3][c]) * rs;
         const float zc = pr.probe_bias ? zs + pr.probe_bias[h * sh.r + c] : zs;
         q += zc * zc;
-        if (i < sh.N) z[c] = zc;
+        zo[c] = zc;
+        if (i < sh.N && !run4) z[c] = zc;
       }
     }
+    if (i < sh.N && run4) *reinterpret_cast<float4*>(z) = make_float4(zo[0], zo[1], zo[2], zo[3]);
     if (i < sh.N) ws.ell[p * ws.s_ell + static_cast<long long>(h) * sh.N + i] = q;
     const float bq = wave_sum(i < sh.N ? q : 0.f);
     if (lane == 0) part[blockIdx.x * sh.hq + h] = bq;
