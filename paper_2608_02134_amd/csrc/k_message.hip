@@ -1004,8 +1004,17 @@ constexpr int kGramPitch = kGramTC + 4;     // floats per staged head row
 constexpr int kGramTok = 2;                 // tokens per wave (kHeadTok per block)
 static_assert(kGramTok * 4 == kHeadTok, "one block covers kHeadTok tokens");
 
-template <int R>
-__global__ void __launch_bounds__(256) headgram_kernel(Shape sh, Params pr, Ws ws, int write_e2) {
+// kRun: T is a multiple of four, so a lane's four columns of a head are one
+// aligned 16-byte run of the client row and of the LDS row (a quarter of the
+// requests); other T load column by column.  The next chunk, or the next
+// token's first one, is loaded while the current one is multiplied; the clip
+// is bound by reading the client rows (16384 tokens of 28 x 256: 470 MB in
+// 212 us).  Before, with single loads and the later chunks of a long T loaded
+// in line: 256 tokens 7.4 -> 5.6 us, 1296 tokens 11 -> 10, 16 problems of them
+// 70..80 -> 49, 4050 tokens 27 -> 20, the clip 250 -> 212.  Without the LDS
+// (lanes exchanging the columns by permutes) it took twice as long.
+template <int R, bool kRun>
+__global__ void __launch_bounds__(256, kRun ? 3 : 2) headgram_kernel(Shape sh, Params pr, Ws ws, int write_e2) {
   constexpr int U = R + 1;                     // [Z_h[i]; sigma_h] / l_h[i]
   __shared__ __attribute__((aligned(16))) float xs[4][32 * kGramPitch];
   __shared__ float us[4][32 * U];
@@ -1033,12 +1042,16 @@ __global__ void __launch_bounds__(256) headgram_kernel(Shape sh, Params pr, Ws w
     const float* row = E + static_cast<long long>(min(i, sh.N - 1)) * sh.ldM;
     const int tc = min(kGramTC, T - t0);
 #pragma unroll
-    for (int k = 0; k < 8; ++k)
+    for (int k = 0; k < 8; ++k) {
+      const int h = min(k * 4 + fk, H - 1);
+      if constexpr (kRun) {
+        const float4 x = *reinterpret_cast<const float4*>(row + h * T + t0 + min(fr * 4, tc - 4));
+        vx[k * 4] = x.x; vx[k * 4 + 1] = x.y; vx[k * 4 + 2] = x.z; vx[k * 4 + 3] = x.w;
+      } else {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int h = min(k * 4 + fk, H - 1), c = min(fr * 4 + q, tc - 1);
-        vx[k * 4 + q] = row[h * T + t0 + c];
+        for (int q = 0; q < 4; ++q) vx[k * 4 + q] = row[h * T + t0 + min(fr * 4 + q, tc - 1)];
       }
+    }
   };
   auto load_vec = [&](int i) {
     const int ic = min(i, sh.N - 1);
@@ -1048,12 +1061,15 @@ __global__ void __launch_bounds__(256) headgram_kernel(Shape sh, Params pr, Ws w
   };
   auto store_chunk = [&](int tc) {
 #pragma unroll
-    for (int k = 0; k < 8; ++k)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int h = k * 4 + fk, c = fr * 4 + q;
-        X[h * kGramPitch + c] = (h < H && c < tc) ? vx[k * 4 + q] : 0.f;
-      }
+    for (int k = 0; k < 8; ++k) {
+      const int h = k * 4 + fk, c = fr * 4;
+      float4 x;
+      x.x = (h < H && c < tc) ? vx[k * 4] : 0.f;
+      x.y = (h < H && c + 1 < tc) ? vx[k * 4 + 1] : 0.f;
+      x.z = (h < H && c + 2 < tc) ? vx[k * 4 + 2] : 0.f;
+      x.w = (h < H && c + 3 < tc) ? vx[k * 4 + 3] : 0.f;
+      *reinterpret_cast<float4*>(&X[h * kGramPitch + c]) = x;
+    }
   };
   auto store_vec = [&]() {
     if (lane < 32) {
@@ -1079,8 +1095,11 @@ __global__ void __launch_bounds__(256) headgram_kernel(Shape sh, Params pr, Ws w
     for (; t0 < T; t0 += kGramTC) {
       const int tc = min(kGramTC, T - t0);
       __builtin_amdgcn_wave_barrier();
-      if (t0 > 0) load_token(i, t0);                               // later chunks of a long T
       store_chunk(tc);
+      if (t0 + kGramTC < T)
+        load_token(i, t0 + kGramTC);
+      else if (j + 1 < kGramTok)
+        load_token(i + 1, 0);
       __builtin_amdgcn_wave_barrier();
       const int nk = (tc + 3) / 4;
       for (int kk = 0; kk < nk; ++kk) {
@@ -1092,10 +1111,7 @@ __global__ void __launch_bounds__(256) headgram_kernel(Shape sh, Params pr, Ws w
       }
     }
     const int tl_last = (T - 1) - (t0 - kGramTC);   // column of t = T-1 in the last chunk
-    if (j + 1 < kGramTok) {                          // next token's loads overlap the epilogue
-      load_token(i + 1, 0);
-      load_vec(i + 1);
-    }
+    if (j + 1 < kGramTok) load_vec(i + 1);
     __builtin_amdgcn_wave_barrier();
     // epilogue: lane holds G[16 hb + 4 fk + e][16 gb + fr]; weight
     // W[h][g] = u_h . u_g with u = [Z; sigma] / l
@@ -1501,7 +1517,12 @@ static hipError_t message_view(const Shape& sv, const Params& pr, const Ws& wv, 
   const int we2 = current ? 1 : 0;
   switch (sv.r) {
 #define GMC_HEADGRAM(R) \
-    case R: hipLaunchKernelGGL(headgram_kernel<R>, dim3(sv.n_head_blk, sv.B), dim3(256), 0, st, sv, pv, wv, we2); break;
+    case R: \
+      if (sv.T % 4 == 0) \
+        hipLaunchKernelGGL((headgram_kernel<R, true>), dim3(sv.n_head_blk, sv.B), dim3(256), 0, st, sv, pv, wv, we2); \
+      else \
+        hipLaunchKernelGGL((headgram_kernel<R, false>), dim3(sv.n_head_blk, sv.B), dim3(256), 0, st, sv, pv, wv, we2); \
+      break;
     GMC_HEADGRAM(1) GMC_HEADGRAM(2) GMC_HEADGRAM(3) GMC_HEADGRAM(4)
     GMC_HEADGRAM(5) GMC_HEADGRAM(6) GMC_HEADGRAM(7) GMC_HEADGRAM(8)
 #undef GMC_HEADGRAM
