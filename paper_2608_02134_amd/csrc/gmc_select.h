@@ -112,10 +112,11 @@ __device__ inline void block_topk256(const uint32_t* keys, int n, int count, int
 // barrier (three histogram buffers rotate).  The block has NW >= 4 waves.
 // The selected indices are written to out[0, count) in ascending index order
 // and out[count, fill) is filled with index 0.
-// hist: 768 ints of LDS, scan: >= 3 NW ints.
+// hist: 768 ints of LDS, scan: >= 3 NW ints.  least (if given, holding the
+// largest word) gets the smallest selected key.
 template <int KPT, int NW = 4>
 __device__ inline void block_topk_regs(const uint32_t (&k)[KPT], int seg, int count, int* out, int* hist, int* scan,
-                                int fill = 64) {
+                                int fill = 64, uint32_t* least = nullptr) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (tid < 256) {
     hist[tid] = 0;
@@ -206,17 +207,23 @@ __device__ inline void block_topk_regs(const uint32_t (&k)[KPT], int seg, int co
   int gt_b = static_cast<int>(static_cast<unsigned>(pre) & 0xFFFFu);
   int eq_b = static_cast<int>(static_cast<unsigned>(pre) >> 16);
   const int i0 = tid * seg;
+  uint32_t low = 0xFFFFFFFFu;
 #pragma unroll
   for (int q = 0; q < KPT; ++q) {
     if (k[q] == 0u) continue;
     if (k[q] > kth) {
       out[gt_b + min(eq_b, remaining)] = i0 + q;
+      low = min(low, k[q]);
       ++gt_b;
     } else if (k[q] == kth) {
-      if (eq_b < remaining) out[gt_b + eq_b] = i0 + q;
+      if (eq_b < remaining) {
+        out[gt_b + eq_b] = i0 + q;
+        low = min(low, k[q]);
+      }
       ++eq_b;
     }
   }
+  if (least && low != 0xFFFFFFFFu) atomicMin(least, low);
   if (tid >= count && tid < fill) out[tid] = 0;
   __syncthreads();
 }
@@ -305,10 +312,12 @@ __device__ __forceinline__ float transpose_reduce64(float* v, int lane) {
 // two for the streamed kernel when it fits twice); block k owns the tokens
 // [k tpb, (k + 1) tpb) and keeps its own copy of the coverage b_m in LDS.  A
 // round:
-//   gains  - u_i of the block's tokens, from client rows held in registers
-//            for the whole call or streamed from the caches; the block's
-//            gains are published together (0 for selected tokens), tagged
-//            with the round
+//   gains  - u_i of the block's tokens that may enter the pool, from client
+//            rows held in registers for the whole call or streamed from the
+//            caches; the block's
+//            gains are published together (0 for the other tokens), tagged
+//            with the pass over them (a round has a second one if the first
+//            left out too many)
 //   pool   - every block that owns a row chunk (and the last block) waits
 //            for the tagged gains and picks the same pool (identical inputs,
 //            deterministic top-k)
@@ -337,7 +346,10 @@ __device__ __forceinline__ float transpose_reduce64(float* v, int lane) {
 // no heartbeat and no same-address atomics.  Every wait is
 // bounded: after kSpinLimit polls, or once this block has recorded a timeout,
 // the block records the timeout (device status word) and stops waiting, so
-// every wave always exits.
+// every wave always exits.  A round's second pass over the gains counts as a
+// round in this: it is published after every read of the first one's gains,
+// by the blocks without the pool after block 0's request, which they answer
+// before block 0 can publish the batch.
 constexpr int kSpinLimit = 1 << 18;   // bounded waits (a fraction of a second)
 constexpr int kSumsQ = 16;            // chunk sums in flight per lane
 constexpr int kCovQ = 16;             // coverage rows in flight per thread
@@ -370,14 +382,25 @@ __device__ __forceinline__ uint32_t low_word(unsigned long long w) { return stat
 __device__ __forceinline__ uint32_t high_word(unsigned long long w) { return static_cast<uint32_t>(w >> 32); }
 __device__ __forceinline__ float untagged(uint32_t w) { return __uint_as_float(w & 0x7FFFFFFFu); }
 
+// Sum over the block's four waves of a wave-uniform count (scan: 4 ints, free
+// again after the next barrier of the caller).
+__device__ __forceinline__ int block_total(int n, int* scan) {
+  if ((threadIdx.x & 63) == 0) scan[threadIdx.x >> 6] = n;
+  __syncthreads();
+  const int t = scan[0] + scan[1] + scan[2] + scan[3];
+  __syncthreads();
+  return t;
+}
+
 // Pool of the persistent selection with the keys in registers: thread t
 // takes the gains of its contiguous segment (an even number of tokens, so
 // that pairs load together; taken tokens key 0), waiting until each carries
-// this round's tag.
-template <int KPT>
-__device__ __forceinline__ void pool_regs(const Shape& sh, const uint32_t* tu, unsigned tb,
+// this round's tag.  LAZY: keys below `floor_key` are left out; false if
+// fewer than psize are left.
+template <int KPT, bool LAZY>
+__device__ __forceinline__ bool pool_regs(const Shape& sh, const uint32_t* tu, unsigned tb,
                                           const unsigned char* taken, int psize, int* pool_s, int* hist, int* scan,
-                                          int* cnt, int* failed) {
+                                          int* cnt, int* failed, uint32_t floor_key, uint32_t* least) {
   static_assert(KPT % 2 == 0, "token pairs");
   const int seg = ((sh.N + 255) / 256 + 1) & ~1;
   const int i0 = threadIdx.x * seg;
@@ -410,7 +433,22 @@ __device__ __forceinline__ void pool_regs(const Shape& sh, const uint32_t* tu, u
     k[2 * q] = need[2 * q] ? score_key(untagged(low_word(w[q]))) : 0u;
     k[2 * q + 1] = need[2 * q + 1] ? score_key(untagged(high_word(w[q]))) : 0u;
   }
-  block_topk_regs<KPT>(k, seg, psize, pool_s, hist, scan);
+  if constexpr (LAZY) {
+    if (threadIdx.x == 0) *least = 0xFFFFFFFFu;
+    if (floor_key) {
+      int n = 0;
+#pragma unroll
+      for (int q = 0; q < KPT; ++q) {
+        if (k[q] < floor_key) k[q] = 0u;
+        n += __popcll(__ballot(k[q] != 0u));
+      }
+      if (block_total(n, scan) < psize) return false;
+    }
+    block_topk_regs<KPT>(k, seg, psize, pool_s, hist, scan, 64, least);
+  } else {
+    block_topk_regs<KPT>(k, seg, psize, pool_s, hist, scan);
+  }
+  return true;
 }
 
 // A wave-uniform value the compiler cannot see through (so it is not
@@ -488,6 +526,30 @@ __device__ __forceinline__ void stream_gains(const float* const (&row)[T], const
     if (ng_main + q < ng) add(ng_main + q, q);
 }
 
+// Gains left out.  b_m only grows, so a token's gain never does (term by term
+// and in every rounded partial sum), and the gain it had when it was last
+// formed bounds it.  A round forms only the gains whose bound reaches a
+// threshold theta that every block knows; the others go out as zero.  If at
+// least a pool's worth of gains reach theta the pool is the one that all
+// gains would give; else the round's gains are formed once more, all of them.
+// The first round, and a call that traces its gains, form all; so do the
+// kernels whose blocks hold all their tokens, as a wave forms the held ones
+// together: with some left out nothing is saved and the rounds that go again
+// are lost (M = 6944: 458 us a call with all gains, 482 so; M = 4692,
+// N = 2580: 769 and 810).
+// theta lies below the smallest gain of the last pool by twice the part that
+// this fell by in the last round: of the document page's 52 rounds 4 go again
+// and 12 % of the gains are formed, with a fixed 0.8 12 rounds and 18 %.  Per
+// call, all gains against these: the document page 1641 and 1469 us, 16
+// problems of 1296 tokens 1228 and 1148.
+constexpr int kLazyList = 768;    // listed tokens at a time (the words of hist)
+constexpr int kLazyAgain = 62, kLazyTheta = 63;   // words of tp beside the batch
+__device__ __forceinline__ float next_threshold(float cut, float last_cut, int r) {
+  const float fall = r > 0 && last_cut > 0.f ? cut / last_cut : 0.8f;
+  const float t = cut * fminf(fmaxf(2.f * fall - 1.f, 0.f), 0.95f);
+  return t > 0.f && t < 3e38f ? t : 0.f;   // (no threshold from infinite gains)
+}
+
 // RES: eight tokens per block (N <= 8 blocks, M <= 256 kResJ) whose weighted
 // client rows alpha_m E[i][m] (Cbar, the product rounded once) stay in
 // registers for the whole call, wave w holding the rows
@@ -496,9 +558,10 @@ __device__ __forceinline__ void stream_gains(const float* const (&row)[T], const
 // R > 0: the rows of each wave's first R tokens stay in registers, up to 256 J
 // rows each; a round's gains read weights and coverage from LDS (measured at
 // M = 6944, two tokens a wave: 2.2 us of gains a round, 12 us streamed).
-// Tokens beyond them, or all with R = 0, are streamed from the caches.
+// Tokens beyond them, or all with R = 0, are streamed from the caches (S; not
+// S: the block has at most 4 R tokens).
 constexpr int kResJ = 14;
-template <bool RES, int J, int R, int PF, bool AL = true>
+template <bool RES, int J, int R, int PF, bool AL = true, bool S = true>
 __device__ __forceinline__ void select_rounds(const Shape& sh, const Params& pr, const Ws& ws, int nblk,
                                               const SelOut& so) {
   extern __shared__ __attribute__((aligned(16))) float dyn[];
@@ -516,6 +579,11 @@ __device__ __forceinline__ void select_rounds(const Shape& sh, const Params& pr,
   __shared__ int hist[768], scan[16], bc[2], failed, rank_s[4][64];
   __shared__ int pool_s[64], chosen[64], bidx[64];
   __shared__ float rmu[4][64], rden_s[4][64], red[16];
+  // gains left out of a round (not with RES): see next_threshold
+  constexpr bool LAZY = !RES && S;
+  __shared__ float theta_s;
+  __shared__ uint32_t cut_s;
+  __shared__ int again_s, nlist_s;
   // Cbar of the chunk's rows at the pool's tokens (pool position, row lane),
   // kept from the responsibilities for the coverage refresh
   __shared__ float cpool[64][64];
@@ -583,7 +651,11 @@ __device__ __forceinline__ void select_rounds(const Shape& sh, const Params& pr,
   int selected = sh.nseed;
   const Shape sh_call = sh;
   const int tid_call = tid;
-  for (int r = 0; r < sh_call.rounds; ++r) {
+  // a trace asks for every gain; a batch above 62 leaves tp no words for the
+  // threshold and the request to go again
+  const bool lazy = LAZY && so.gains == nullptr && sh.b <= kLazyAgain;
+  float theta = 0.f, cut = 0.f;
+  for (int r = 0, it = 0; r < sh_call.rounds; ++it) {
     // Opaque per-round copies of the shape and the thread index: index math
     // derived from them is redone every round instead of being hoisted out
     // of the loop and kept live (in spill registers) across all rounds.
@@ -601,8 +673,12 @@ __device__ __forceinline__ void select_rounds(const Shape& sh, const Params& pr,
     const int bsize = min(sh.b, sh.K - selected);
     const unsigned tag = static_cast<unsigned>(r + 1);
     unsigned long long picked = 0;   // pool positions of the batch
-    const unsigned tb = round_tag(r);
-    uint32_t* tur = tu + (r & 1) * handoff_stride(sh.N);
+    const unsigned tb = round_tag(r), tbu = round_tag(it);
+    uint32_t* tur = tu + (it & 1) * handoff_stride(sh.N);
+    // whether the block's token l (at t0 + l) needs its gain now
+    auto needs = [&](int l) {
+      return l < tpb && t0 + l < sh.N && !taken[t0 + l] && (theta <= 0.f || gsum[l] >= theta);
+    };
     uint32_t* tsr = ts + (r & 1) * 64LL * nchunk;
 
     // ---- singleton gains of unselected tokens, two tokens per wave pass with
@@ -634,12 +710,16 @@ __device__ __forceinline__ void select_rounds(const Shape& sh, const Params& pr,
         const int t = blk * 8 + tid;
         const float g = ((rmu[0][tid] + rmu[1][tid]) + rmu[2][tid]) + rmu[3][tid];
         const float u = t < sh.N && !taken[t] ? g : 0.f;
-        if (t < sh.N) st_tagged(&tur[t], tb, u);
+        if (t < sh.N) st_tagged(&tur[t], tbu, u);
         if (so.gains && t < sh.N) so.gains[(static_cast<long long>(p) * sh.rounds + r) * sh.N + t] = u;
       }
     }
     if constexpr (R > 0) {
       // the held tokens: each sum is formed exactly as for a streamed token
+      bool any = false;
+#pragma unroll
+      for (int s = 0; s < R; ++s) any |= needs(4 * s + wave);
+      if (!LAZY || __any(any)) {
       float acc[R];
 #pragma unroll
       for (int s = 0; s < R; ++s) acc[s] = 0.f;
@@ -669,52 +749,64 @@ __device__ __forceinline__ void select_rounds(const Shape& sh, const Params& pr,
 #pragma unroll
         for (int s = 0; s < R; ++s)
           if (4 * s + wave < tpb) gsum[4 * s + wave] = acc[s];
+      }
     }
-    if constexpr (RES) {
-    } else {
-      // streamed tokens, T at a time
-      auto pass = [&](auto tt, int s0) {
-        constexpr int T = decltype(tt)::value;
-        int it[T];
-        bool ok[T];
-        int any = -1;
-#pragma unroll
-        for (int k = T - 1; k >= 0; --k) {
-          const int l = 4 * (s0 + k) + wave;
-          it[k] = t0 + l;
-          ok[k] = l < tpb && it[k] < sh.N && taken[min(it[k], sh.N - 1)] == 0;
-          any = ok[k] ? it[k] : any;
+    if constexpr (!RES) {
+      // the block's other tokens that need a gain, listed by its first wave
+      // and dealt to the waves, T at a time
+      int* list = hist;   // free between the pools
+      for (int w0 = 4 * R; S && w0 < tpb; w0 += kLazyList) {
+        const int w1 = min(tpb, w0 + kLazyList);
+        if (wave == 0) {
+          int n = 0;
+          for (int l0 = w0; l0 < w1; l0 += 64) {
+            const int l = l0 + lane;
+            const bool nd = l < w1 && needs(l);
+            const unsigned long long mask = __ballot(nd);
+            if (nd) list[n + __popcll(mask & ((1ull << lane) - 1ull))] = l;
+            n += __popcll(mask);
+          }
+          if (lane == 0) nlist_s = n;
         }
-        if (any < 0) return;
-        // a token that needs no gain re-reads a needed one's row (cache hits)
-        const float* row[T];
-        float acc[T];
+        __syncthreads();
+        const int n = __builtin_amdgcn_readfirstlane(nlist_s);
+        auto pass = [&](auto tt, int s0) {
+          constexpr int T = decltype(tt)::value;
+          int l[T];
+          const float* row[T];
+          float acc[T];
 #pragma unroll
-        for (int k = 0; k < T; ++k) {
-          row[k] = E + static_cast<long long>(ok[k] ? it[k] : any) * sh.ldM;
-          acc[k] = 0.f;
-        }
-        stream_gains<T, T == 4 ? PF : 2 * PF, AL>(row, AL ? al : alpha_g, bl, ng, sh.m, sh.ldM - 4, lane, acc);
+          for (int k = 0; k < T; ++k) {
+            // past the list's end its last token again (cache hits)
+            l[k] = __builtin_amdgcn_readfirstlane(list[min(4 * (s0 + k) + wave, n - 1)]);
+            row[k] = E + static_cast<long long>(t0 + l[k]) * sh.ldM;
+            acc[k] = 0.f;
+          }
+          stream_gains<T, T == 4 ? PF : T == 2 ? 2 * PF : 4 * PF, AL>(row, AL ? al : alpha_g, bl, ng, sh.m, sh.ldM - 4,
+                                                                     lane, acc);
 #pragma unroll
-        for (int k = 0; k < T; ++k) acc[k] = wave_sum(acc[k]);
-        if (lane == 0)
+          for (int k = 0; k < T; ++k) acc[k] = wave_sum(acc[k]);
+          if (lane == 0)
 #pragma unroll
-          for (int k = 0; k < T; ++k)
-            if (ok[k]) gsum[4 * (s0 + k) + wave] = acc[k];
-      };
-      const int ns = (tpb - wave + 3) / 4;   // the wave's tokens
-      int s0 = R;
-      if constexpr (R == 0)
-        for (; s0 + 2 < ns; s0 += 4) pass(std::integral_constant<int, 4>{}, s0);
-      for (; s0 < ns; s0 += 2) pass(std::integral_constant<int, 2>{}, s0);
+            for (int k = 0; k < T; ++k)
+              if (4 * (s0 + k) + wave < n) gsum[l[k]] = acc[k];
+        };
+        const int ns = (n - wave + 3) / 4;   // the wave's tokens
+        int s0 = 0;
+        if constexpr (R == 0)
+          for (; s0 + 2 < ns; s0 += 4) pass(std::integral_constant<int, 4>{}, s0);
+        for (; s0 + 1 < ns; s0 += 2) pass(std::integral_constant<int, 2>{}, s0);
+        if (s0 < ns) pass(std::integral_constant<int, 1>{}, s0);
+        if (w1 < tpb) __syncthreads();   // the list is rewritten
+      }
       // the block's gains leave together: its words share cache lines with
       // few other blocks, and stores to one line from several XCDs serialise
       __syncthreads();
       for (int l = tid; l < tpb; l += 256) {
         const int t = t0 + l;
         if (t >= sh.N) break;
-        const float u = taken[t] ? 0.f : gsum[l];
-        st_tagged(&tur[t], tb, u);
+        const float u = !taken[t] && (!LAZY || gsum[l] >= theta) ? gsum[l] : 0.f;
+        st_tagged(&tur[t], tbu, u);
         if (so.gains) so.gains[(static_cast<long long>(p) * sh.rounds + r) * sh.N + t] = u;
       }
     }
@@ -723,22 +815,27 @@ __device__ __forceinline__ void select_rounds(const Shape& sh, const Params& pr,
     //      round's gains)
     // the batch's tokens, published by block 0 for the blocks without the pool
     unsigned long long* tpr = ws.tp + p * ws.s_tp + (r & 1) * 64;
+    const uint32_t floor_key = LAZY && theta > 0.f ? score_key(theta) : 0u;
+    float theta_next = 0.f;
     if (pool_here) {
+    bool whole = true;   // the pool is certain
     if constexpr (RES) {
       if (sh.N <= 256 * 6)
-        pool_regs<6>(sh, tur, tb, taken, psize, pool_s, hist, scan, cnt, &failed);
+        pool_regs<6, LAZY>(sh, tur, tbu, taken, psize, pool_s, hist, scan, cnt, &failed, 0u, nullptr);
       else
-        pool_regs<8>(sh, tur, tb, taken, psize, pool_s, hist, scan, cnt, &failed);
+        pool_regs<8, LAZY>(sh, tur, tbu, taken, psize, pool_s, hist, scan, cnt, &failed, 0u, nullptr);
     } else if (sh.N <= 256 * 8)
-      pool_regs<8>(sh, tur, tb, taken, psize, pool_s, hist, scan, cnt, &failed);
+      whole = pool_regs<8, LAZY>(sh, tur, tbu, taken, psize, pool_s, hist, scan, cnt, &failed, floor_key, &cut_s);
     else if (sh.N <= 256 * 16)
-      pool_regs<16>(sh, tur, tb, taken, psize, pool_s, hist, scan, cnt, &failed);
+      whole = pool_regs<16, LAZY>(sh, tur, tbu, taken, psize, pool_s, hist, scan, cnt, &failed, floor_key, &cut_s);
     else {
+      int n = 0;
+      if (tid == 0) cut_s = 0xFFFFFFFFu;
       for (int base = 0; base < sh.N; base += 256 * 16) {
         unsigned long long w[8];
         auto at = [&](int q) { return min(base + 2 * (q * 256 + tid), (sh.N - 1) & ~1); };
         auto stale = [&](int q) {
-          return is_stale(low_word(w[q]), tb) || (at(q) + 1 < sh.N && is_stale(high_word(w[q]), tb));
+          return is_stale(low_word(w[q]), tbu) || (at(q) + 1 < sh.N && is_stale(high_word(w[q]), tbu));
         };
 #pragma unroll
         for (int q = 0; q < 8; ++q) w[q] = ld_tagged2(&tur[at(q)]);
@@ -756,12 +853,28 @@ __device__ __forceinline__ void select_rounds(const Shape& sh, const Params& pr,
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
           const int i = base + 2 * (q * 256 + tid);
-          if (i < sh.N) keys[i] = taken[i] ? 0u : score_key(untagged(low_word(w[q])));
-          if (i + 1 < sh.N) keys[i + 1] = taken[i + 1] ? 0u : score_key(untagged(high_word(w[q])));
+          uint32_t k0 = i < sh.N && !taken[i] ? score_key(untagged(low_word(w[q]))) : 0u;
+          uint32_t k1 = i + 1 < sh.N && !taken[i + 1] ? score_key(untagged(high_word(w[q]))) : 0u;
+          k0 = k0 < floor_key ? 0u : k0;
+          k1 = k1 < floor_key ? 0u : k1;
+          n += __popcll(__ballot(k0 != 0u)) + __popcll(__ballot(k1 != 0u));
+          if (i < sh.N) keys[i] = k0;
+          if (i + 1 < sh.N) keys[i + 1] = k1;
         }
       }
-      __syncthreads();
-      block_topk256(keys, sh.N, psize, pool_s, hist, scan, bc);
+      whole = block_total(n, scan) >= psize || floor_key == 0u;   // (the keys are in LDS)
+      if (whole) {
+        block_topk256(keys, sh.N, psize, pool_s, hist, scan, bc);
+        if (tid < psize) atomicMin(&cut_s, keys[pool_s[tid]]);
+      }
+    }
+    if constexpr (LAZY) {
+      if (!whole && !failed) {
+        // too few gains reached the threshold: once more with all of them
+        if (pool_pub && blk == 0 && tid == 0) st_dev64(&tpr[kLazyAgain], tag_value(tag, 0.f));
+        theta = 0.f;
+        continue;
+      }
     }
     if constexpr (!RES) {
       // clamp to valid rows (defensive) and pad past psize with a valid row,
@@ -771,6 +884,11 @@ __device__ __forceinline__ void select_rounds(const Shape& sh, const Params& pr,
       __syncthreads();
       if (tid < 64) pool_s[tid] = pv;
       __syncthreads();
+    }
+    if constexpr (LAZY) {
+      const float last_cut = cut;
+      cut = __uint_as_float(cut_s - 1u);
+      theta_next = lazy ? next_threshold(cut, last_cut, r) : 0.f;
     }
     }
     if (blk == nblk - 1 && so.pool) {
@@ -836,20 +954,39 @@ __device__ __forceinline__ void select_rounds(const Shape& sh, const Params& pr,
     //      flight) and adds them in chunk order; the quarters are added in
     //      wave order.  The other blocks wait for the batch's tokens alone.
     if (!pool_here) {
-      // nothing left for these blocks in the last round
-      if (r + 1 == sh.rounds) break;
-      if (tid < bsize) {
-        unsigned long long bw = ld_dev64(&tpr[tid]);
-        for (int spin = 0; tag_of(bw) != tag && !failed; ++spin) {
+      // nothing left for these blocks in the last round, unless its gains may
+      // be asked for once more
+      if (r + 1 == sh.rounds && (!LAZY || theta <= 0.f)) break;
+      if (wave == 0) {
+        const bool mine = lane < bsize || (lazy && lane == kLazyTheta);
+        const bool poll = mine || (theta > 0.f && lane == kLazyAgain);
+        unsigned long long bw = poll ? ld_dev64(&tpr[lane]) : 0ull;
+        bool again = false;
+        for (int spin = 0;; ++spin) {
+          again = LAZY && __any(theta > 0.f && lane == kLazyAgain && tag_of(bw) == tag);
+          if (again || !__any(mine && tag_of(bw) != tag) || failed) break;
           if (spin == kSpinLimit) { mark_timeout(cnt, &failed); break; }
           __builtin_amdgcn_s_sleep(1);
-          bw = ld_dev64(&tpr[tid]);
+          if (poll && tag_of(bw) != tag) bw = ld_dev64(&tpr[lane]);
         }
-        const int i = min(max(__float_as_int(value_of(bw)), 0), sh.N - 1);
-        bidx[tid] = i;
-        taken[i] = 1;
+        if constexpr (LAZY) {
+          if (lane == 0) again_s = again ? 1 : 0;
+          if (lane == kLazyTheta) theta_s = lazy ? value_of(bw) : 0.f;
+        }
+        if (lane < bsize && !again) {
+          const int i = min(max(__float_as_int(value_of(bw)), 0), sh.N - 1);
+          bidx[lane] = i;
+          taken[i] = 1;
+        }
       }
       __syncthreads();
+      if constexpr (LAZY) {
+        if (again_s) {
+          theta = 0.f;
+          continue;
+        }
+        theta_next = theta_s;
+      }
     } else {
     {
       const int per = (nchunk + 3) / 4;
@@ -905,6 +1042,7 @@ __device__ __forceinline__ void select_rounds(const Shape& sh, const Params& pr,
         taken[i] = 1;
         if (pool_pub && blk == 0) st_dev64(&tpr[k], tag_value(tag, __int_as_float(i)));
       }
+      if (lazy && pool_pub && blk == 0 && tid == kLazyTheta) st_dev64(&tpr[kLazyTheta], tag_value(tag, theta_next));
     }
     }
     const bool last = r + 1 == sh.rounds;
@@ -979,6 +1117,8 @@ __device__ __forceinline__ void select_rounds(const Shape& sh, const Params& pr,
       }
       __syncthreads();
       selected += bsize;
+      theta = theta_next;
+      ++r;
       continue;
     }
 
@@ -1081,11 +1221,11 @@ select_split_kernel(Shape sh, Params pr, Ws ws, int nblk, SelOut so) {
 // up to 512 registers, but J R is kept near 75: the next call's gate block of
 // the bank stream waits beside this kernel, possibly on the same CU, and a
 // grid of one block per CU must still become resident (four waves of the
-// gate need 32 registers per SIMD; these kernels take at most 436 of 512).
-template <int J, int R>
+// gate need 32 registers per SIMD; these kernels take at most 468 of 512).
+template <int J, int R, bool S>
 static __global__ void __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(1, 1)))
 select_hold_kernel(Shape sh, Params pr, Ws ws, int nblk, SelOut so) {
-  select_rounds<false, J, R, 2>(sh, pr, ws, nblk, so);
+  select_rounds<false, J, R, 2, true, S>(sh, pr, ws, nblk, so);
 }
 
 }  // namespace gmc

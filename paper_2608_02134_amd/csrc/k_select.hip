@@ -563,15 +563,18 @@ static void launch_cov(const Shape& sh, const Ws& ws, int nb, hipStream_t st) {
 struct SelVariant {
   const void* fn;
   int J, R;            // rows / 256 and tokens per wave held in registers (0: none)
+  bool streams;        // takes more tokens than the held ones
   int lds;             // dynamic LDS the occupancy below was asked for (-1: not yet)
   int per_cu;
 };
 enum { kSelStream, kSelWide, kSelSplit, kSelHold };   // g_sel: hold variants by J, then R
 static SelVariant g_sel[] = {
-    {reinterpret_cast<const void*>(select_stream_kernel), 0, 0, -1, 0},
-    {reinterpret_cast<const void*>(select_wide_kernel), 0, 0, -1, 0},
-    {reinterpret_cast<const void*>(select_split_kernel), 0, 0, -1, 0},
-#define GMC_HOLD(J, R) {reinterpret_cast<const void*>(select_hold_kernel<J, R>), J, R, -1, 0},
+    {reinterpret_cast<const void*>(select_stream_kernel), 0, 0, true, -1, 0},
+    {reinterpret_cast<const void*>(select_wide_kernel), 0, 0, true, -1, 0},
+    {reinterpret_cast<const void*>(select_split_kernel), 0, 0, false, -1, 0},
+#define GMC_HOLD(J, R)                                                               \
+  {reinterpret_cast<const void*>(select_hold_kernel<J, R, false>), J, R, false, -1, 0}, \
+  {reinterpret_cast<const void*>(select_hold_kernel<J, R, true>), J, R, true, -1, 0},
     GMC_HOLD(4, 5) GMC_HOLD(8, 5) GMC_HOLD(14, 3) GMC_HOLD(14, 5) GMC_HOLD(20, 2) GMC_HOLD(20, 3) GMC_HOLD(24, 3)
     GMC_HOLD(28, 2) GMC_HOLD(32, 2) GMC_HOLD(36, 2) GMC_HOLD(48, 1)
 #undef GMC_HOLD
@@ -643,7 +646,7 @@ static SelPlan select_plan(const Shape& sh) {
   if (one >= 1) {
     // rows in registers: the narrowest variant the rows fit, of those the
     // fewest tokens per wave that cover the block's, else the most.  Held
-    // rows win wherever they were measured, from one image (M = 6944: 460
+    // rows win wherever they were measured with all gains formed, from one image (M = 6944: 460
     // against 496 us per call; M = 4692, N = 2580: 767 against 915; the
     // document page 1673 against 1994) to sixteen (1271 against 1296, 31 % of
     // the tokens held).
@@ -651,7 +654,7 @@ static SelPlan select_plan(const Shape& sh) {
     SelVariant* best = nullptr;
     for (int i = kSelHold; i < static_cast<int>(sizeof(g_sel) / sizeof(g_sel[0])); ++i) {
       SelVariant& v = g_sel[i];
-      if (256 * v.J < sh.m || (best && (v.J > best->J || best->R >= tokens))) continue;
+      if (256 * v.J < sh.m || v.streams != (tokens > v.R) || (best && (v.J > best->J || best->R >= tokens))) continue;
       best = &v;
     }
     if (best && take(*best, nblk, 1)) return pl;

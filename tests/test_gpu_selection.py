@@ -59,3 +59,38 @@ def test_batches_above_sixteen():
     pr.close()
     check_problem(prob.hidden[0], prob.text_q[0], prob.vis_k[0], prob.pos3d[0], prob.probe, prob.k, outs[0],
                   prob.workload.dtype, O.GmcParams(batch_b=32, pool_mult=2))
+
+
+# batch, grid, queries, budget, overrides: shapes whose blocks stream tokens,
+# where a call that traces its gains forms all of them and a plain one leaves
+# out those that cannot enter the pool
+LEFT_OUT = {
+    "held_and_streamed": (16, (1, 19, 21), 16, 120, {}),
+    "held_and_streamed_wide_rows": (8, (1, 20, 25), 700, 200, {}),
+    "streamed": (2, (1, 11, 12), 1600, 100, {}),
+    "weights_in_memory": (2, (1, 9, 11), 2400, 90, {}),
+    "page": (1, (1, 64, 64), 40, 700, {}),
+    "keys_in_memory": (1, (2, 50, 50), 24, 300, {"batch_b_bounded": 16}),
+    "batch_of_62": (16, (1, 19, 21), 16, 200, {"batch_b": 62, "pool_mult": 1}),
+    "batch_of_64": (16, (1, 19, 21), 16, 200, {"batch_b": 64, "pool_mult": 1}),
+    "batch_of_1": (16, (1, 19, 21), 16, 60, {"batch_b": 1}),
+}
+
+
+@pytest.mark.parametrize("same", [False, True], ids=["drawn", "equal_tokens"])
+@pytest.mark.parametrize("case", list(LEFT_OUT))
+def test_gains_left_out(case, same):
+    """A plain call selects what the traced one does: bit for bit, as the
+    gains that both form are the same sums."""
+    batch, grid, t, k, over = LEFT_OUT[case]
+    prob = synth.make_problem("tiny", batch=batch, grid=grid, t=t, k=k)
+    if same:   # every gain but those of a few tokens vanishes after the first picks
+        prob.hidden[:, 3:] = prob.hidden[:, 3:4]
+        prob.vis_k[:, 3:] = prob.vis_k[:, 3:4]
+    print(f"\n[case] gains left out {case}: N={prob.workload.n} K={k} equal={same}", flush=True)
+    full, pr = run(prob, torch, **over)
+    plain, _ = run(prob, torch, trace=False, pruner=pr)
+    pr.close()
+    for b in range(batch):
+        for key in ("out_idx", "out_pos", "out_hidden"):
+            assert (full[b][key] == plain[b][key]).all(), (case, b, key)
