@@ -457,11 +457,12 @@ __global__ void __launch_bounds__(64 * kRsW) rowstat_kernel(Shape sh, Params pr,
 }
 
 // Large pools: one wave per pool position sums rho R over all client rows;
-// the last block picks the batch.
+// the last block picks the batch, with the keys in registers (at most 2048
+// positions; from keys in LDS the kernel took 35.6 us at M = 11520 and 26.5 at
+// M = 5752, now 32.2 and 22.7: the pick is most of what is left).
 __global__ void __launch_bounds__(256)
 colsum_kernel(Shape sh, Ws ws, int round, int psize, int bsize, int sel_base, SelOut so) {
-  extern __shared__ uint32_t keys[];   // pool_cap words
-  __shared__ int hist[512], scan[16], bc[2], flag;
+  __shared__ int hist[768], scan[16], flag;
   __shared__ int chosen[1024];
   const int p = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int jj = blockIdx.x * 4 + wave;
@@ -492,22 +493,22 @@ colsum_kernel(Shape sh, Ws ws, int round, int psize, int bsize, int sel_base, Se
   int* cnt = ws.cnt + p * ws.s_cnt;
   if (!last_arrival(&cnt[4], gridDim.x, &flag)) return;
   if (tid == 0) st_dev(&cnt[4], 0);
-  {
-    float g[8];
+  // thread t owns the positions [t seg, t seg + seg)
+  const int seg = (psize + 255) / 256;
+  float g[8];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) g[q] = ld_dev(&sv[min(q * 256 + tid, psize - 1)]);
+  for (int q = 0; q < 8; ++q) g[q] = ld_dev(&sv[min(tid * seg + min(q, seg - 1), psize - 1)]);
+  uint32_t key[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) key[q] = q < seg && tid * seg + q < psize ? score_key(g[q]) : 0u;
+  if (so.scores) {
+    float* sc = so.scores + (static_cast<long long>(p) * sh.rounds + round) * sh.pool_cap;
 #pragma unroll
     for (int q = 0; q < 8; ++q)
-      if (q * 256 + tid < psize) keys[q * 256 + tid] = score_key(g[q]);
-    if (so.scores) {
-      float* sc = so.scores + (static_cast<long long>(p) * sh.rounds + round) * sh.pool_cap;
-#pragma unroll
-      for (int q = 0; q < 8; ++q)
-        if (q * 256 + tid < sh.pool_cap) sc[q * 256 + tid] = q * 256 + tid < psize ? g[q] : 0.f;
-    }
+      if (key[q]) sc[tid * seg + q] = g[q];
+    for (int j = psize + tid; j < sh.pool_cap; j += 256) sc[j] = 0.f;
   }
-  __syncthreads();
-  block_topk256(keys, psize, bsize, chosen, hist, scan, bc);
+  block_topk_regs<8>(key, seg, bsize, chosen, hist, scan, 0);
   commit_batch(sh, ws, p, round, bsize, sel_base, pool, chosen, so.batch);
 }
 
@@ -646,10 +647,10 @@ static SelPlan select_plan(const Shape& sh) {
   if (one >= 1) {
     // rows in registers: the narrowest variant the rows fit, of those the
     // fewest tokens per wave that cover the block's, else the most.  Held
-    // rows win wherever they were measured with all gains formed, from one image (M = 6944: 460
-    // against 496 us per call; M = 4692, N = 2580: 767 against 915; the
-    // document page 1673 against 1994) to sixteen (1271 against 1296, 31 % of
-    // the tokens held).
+    // rows win wherever they were measured (with all gains formed), from one
+    // image (M = 6944: 460 against 496 us per call; M = 4692, N = 2580: 767
+    // against 915; the document page 1673 against 1994) to sixteen (1271
+    // against 1296, 31 % of the tokens held).
     const int nblk = full(one), tokens = ((sh.N + nblk - 1) / nblk + 3) / 4;
     SelVariant* best = nullptr;
     for (int i = kSelHold; i < static_cast<int>(sizeof(g_sel) / sizeof(g_sel[0])); ++i) {
@@ -767,8 +768,7 @@ hipError_t launch_selection(const Shape& sh, const Params& pr, const Ws& ws, con
                            psize);
       else {
         hipLaunchKernelGGL(rowstat_kernel, dim3((sh.m + 63) / 64, sh.B), dim3(64 * kRsW), 0, st, sh, pr, ws, psize);
-        hipLaunchKernelGGL(colsum_kernel, dim3((psize + 3) / 4, sh.B), dim3(256),
-                           static_cast<size_t>(sh.pool_cap) * sizeof(uint32_t), st, sh, ws, r, psize, bsize,
+        hipLaunchKernelGGL(colsum_kernel, dim3((psize + 3) / 4, sh.B), dim3(256), 0, st, sh, ws, r, psize, bsize,
                            selected, so);
       }
       if (sh.pool_cap <= 64)

@@ -94,3 +94,16 @@ def test_gains_left_out(case, same):
     for b in range(batch):
         for key in ("out_idx", "out_pos", "out_hidden"):
             assert (full[b][key] == plain[b][key]).all(), (case, b, key)
+
+
+@pytest.mark.parametrize("b,mult,k", [(17, 4, 60), (64, 4, 300), (65, 4, 200), (100, 3, 250), (512, 4, 3000),
+                                      (1000, 2, 2100)])
+def test_large_pools(b, mult, k):
+    """Pools above 64: segments of one to eight positions per thread, partial
+    ones, and a last round with fewer tokens left than the pool holds."""
+    prob = synth.make_problem("tiny", grid=(1, 17, 242), t=3, k=k)
+    print(f"\n[case] large pools: N={prob.workload.n} b={b} pool={b * mult} K={k}", flush=True)
+    outs, pr = run(prob, torch, batch_b_bounded=b, pool_mult=mult)
+    pr.close()
+    check_problem(prob.hidden[0], prob.text_q[0], prob.vis_k[0], prob.pos3d[0], prob.probe, prob.k, outs[0],
+                  prob.workload.dtype, O.GmcParams(batch_b_bounded=b, pool_mult=mult), app_proj=prob.app_proj)
