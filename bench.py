@@ -42,7 +42,8 @@ WORKLOAD_TEXT = {
 
 # Sources whose change invalidates a stored PMC traffic measurement of the
 # selection kernels.
-TRAFFIC_SOURCES = ["paper_2608_02134_amd/csrc/k_select.hip", "paper_2608_02134_amd/csrc/gmc_device.h",
+TRAFFIC_SOURCES = ["paper_2608_02134_amd/csrc/k_select.hip", "paper_2608_02134_amd/csrc/gmc_select.h",
+                   "paper_2608_02134_amd/csrc/gmc_device.h",
                    "paper_2608_02134_amd/csrc/gmc_internal.h", "paper_2608_02134_amd/csrc/gmc_api.hip"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 
