@@ -1013,8 +1013,15 @@ static_assert(kGramTok * 4 == kHeadTok, "one block covers kHeadTok tokens");
 // in line: 256 tokens 7.4 -> 5.6 us, 1296 tokens 11 -> 10, 16 problems of them
 // 70..80 -> 49, 4050 tokens 27 -> 20, the clip 250 -> 212.  Without the LDS
 // (lanes exchanging the columns by permutes) it took twice as long.
+//
+// Registers grow with R, so the blocks asked for per CU fall with it: three
+// need at most 168 registers (R <= 4 with runs), two 256, and one leaves them
+// free where two would spill (16 problems of 1296 x 64 columns, a whole call:
+// R = 6 with three blocks 1204 us, with two 873; R = 8 1184 and 918).
+constexpr int gram_blocks(int R, bool run) { return run ? (R <= 4 ? 3 : 2) : (R <= 6 ? 2 : 1); }
+
 template <int R, bool kRun>
-__global__ void __launch_bounds__(256, kRun ? 3 : 2) headgram_kernel(Shape sh, Params pr, Ws ws, int write_e2) {
+__global__ void __launch_bounds__(256, gram_blocks(R, kRun)) headgram_kernel(Shape sh, Params pr, Ws ws, int write_e2) {
   constexpr int U = R + 1;                     // [Z_h[i]; sigma_h] / l_h[i]
   __shared__ __attribute__((aligned(16))) float xs[4][32 * kGramPitch];
   __shared__ float us[4][32 * U];
