@@ -491,6 +491,8 @@ int gmc_gather_rows(int64_t n_tensors, const void* const* src, void* const* dst,
  *            no side stream
  * Every call on a device shares that device's array and clears the region it
  * uses first: calls that overlap on one device race and give wrong results.
+ * A call may run beside the context's calls on other streams; where their
+ * selection kernels do not fit the device side by side they take turns on it.
  * No diagnostics (gmc_get_diag reports on context calls only).  Errors:
  * GMC_ERR_ARG, GMC_ERR_CAPACITY (the call's workspace exceeds the array;
  * nothing is enqueued), GMC_ERR_HIP.

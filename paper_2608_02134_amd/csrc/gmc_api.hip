@@ -579,6 +579,8 @@ int make_shape(const Context& c, int64_t B, int64_t N, int64_t T, int64_t K_req,
 
 namespace gmc {
 
+std::unique_lock<std::mutex> lock_enqueue() { return std::unique_lock<std::mutex>(g_mu); }
+
 int resolve_shape(const gmc_config& g, const Limits& cap, int64_t B, int64_t N, int64_t T, int64_t K_req,
                   Shape* out, int64_t n_hist, int64_t n_images) {
   if (B < 1) return fail(GMC_ERR_ARG, "batch=%lld must be >= 1", static_cast<long long>(B));
@@ -783,7 +785,7 @@ int enqueue_prune(const gmc_config& cfg, const Params& pr0, const Ws& ws, const 
     if (err != hipSuccess) return fail(GMC_ERR_HIP, "image seeds: %s", hipGetErrorString(err));
   }
   bool support_ready = false;
-  err = launch_selection(s, pr, ws, so, st, &support_ready);
+  err = launch_selection(s, pr, ws, so, ps.party, st, &support_ready);
   if (err != hipSuccess) return fail(GMC_ERR_HIP, "selection kernels: %s", hipGetErrorString(err));
   err = launch_assignment(s, pr, ws, hidden, support_ready, tr.assign, st);
   if (err != hipSuccess) return fail(GMC_ERR_HIP, "assignment kernels: %s", hipGetErrorString(err));
@@ -843,7 +845,7 @@ int run(int64_t B, const void* hidden, const void* text_q, const void* vis_k, co
   c.last_cert = false;
   // stage timing keeps every kernel on the caller's stream, so each stage's
   // span measures that stage alone
-  PathStreams ps{st, g_timer.on ? nullptr : c.side, 0, c.fork, c.join};
+  PathStreams ps{st, g_timer.on ? nullptr : c.side, 0, c.fork, c.join, kPartyContext};
   if (ps.side && s.B == 1 && s.K < s.N) {
     c.call_tag = c.call_tag == 0x7fffffff ? 1 : c.call_tag + 1;
     ps.call_tag = c.call_tag;

@@ -150,7 +150,54 @@ struct SelOut {
   float* scores;    // [pool_cap]
 };
 
+// Turns of the persistent selections on one device.  Their blocks wait for each
+// other, so a grid must become resident as a whole: two grids that start
+// together and do not fit the device side by side could each keep part of it
+// until the bounded waits give up.  At most two are in flight, one of the
+// context (its calls run one after another) and one of the static entry point
+// (its calls must not overlap).  Either both fit (see select_plan), or the
+// context's takes a turn on the device: a word that a static call holds from
+// its first kernel to the end of its selection, and such a context call during
+// its selection.  Single waves of few registers wait (kWaitRegs), which leaves
+// the holder's grid room on their CU, and the holder never waits for the other.
+// The waits are bounded (2 s); a call that waited in vain takes the turn, and
+// its selection's own bounded waits note a grid that never became resident.
+// The words work under graph replay too, where the host has no part.
+enum { kPartyContext = 1, kPartyStatic = 2 };
+struct SelTurn {
+  int* words;   // owner (0: none) | problems in flight, per party; null: no turn taken
+  int party;
+};
+
 #ifdef __HIPCC__
+// One lane: waits for the turn and takes it for a selection of `problems`.
+__device__ __forceinline__ void take_turn(const SelTurn& t, int problems) {
+  const unsigned long long t0 = static_cast<unsigned long long>(wall_clock64());
+  for (;;) {
+    int free = 0;
+    if (__hip_atomic_compare_exchange_strong(&t.words[0], &free, t.party, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT) ||
+        free == t.party)
+      break;
+    if (static_cast<unsigned long long>(wall_clock64()) - t0 > kJoinWaitTicks) {
+      __hip_atomic_store(&t.words[0], t.party, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      break;
+    }
+    __builtin_amdgcn_s_sleep(16);
+  }
+  __hip_atomic_store(&t.words[t.party], problems, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void leave_turn(const SelTurn& t) {
+  int own = t.party;
+  __hip_atomic_compare_exchange_strong(&t.words[0], &own, 0, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+}
+// One lane of every problem's last block, at the end of its selection.
+__device__ __forceinline__ void problem_done(const SelTurn& t) {
+  if (t.words && __hip_atomic_fetch_sub(&t.words[t.party], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 1)
+    leave_turn(t);
+}
+
 // Records device status bits of problem p's counters (sticky OR).
 __device__ __forceinline__ void raise_status(int* cnt, unsigned bits) {
   __hip_atomic_fetch_or(reinterpret_cast<unsigned*>(&cnt[kCntStatus]), bits, __ATOMIC_RELAXED,

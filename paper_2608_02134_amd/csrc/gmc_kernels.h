@@ -53,9 +53,15 @@ hipError_t launch_banks(const Shape& sh, const Params& pr, const Ws& ws, const v
 // All selection rounds, then the final coverage and objective values.
 // *support_ready reports that the support list and slots were written too.
 // `so` receives each round's pool, batch, gains and pool scores (any may be
-// NULL).
-hipError_t launch_selection(const Shape& sh, const Params& pr, const Ws& ws, const SelOut& so, hipStream_t st,
-                            bool* support_ready);
+// NULL).  party: whose call this is (see SelTurn); a static call's turn, taken
+// by its first kernel, is left here.
+hipError_t launch_selection(const Shape& sh, const Params& pr, const Ws& ws, const SelOut& so, int party,
+                            hipStream_t st, bool* support_ready);
+
+// The current device's turn words.
+hipError_t selection_turn(int** words);
+// Leaves a turn, if this party holds it.
+hipError_t launch_leave_turn(const SelTurn& turn, hipStream_t st);
 
 // Certificate of the selection rounds from the exported per-round pools,
 // batches, gains and scores (all of `so` set; sh.rounds <= ws.cert_rounds).

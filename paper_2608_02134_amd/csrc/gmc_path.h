@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <mutex>
+
 #include "gmc.h"
 #include "gmc_internal.h"
 
@@ -19,12 +21,19 @@ struct Limits {
 // Streams of one call: everything runs on `st`; with `side` set the bank
 // kernels run there, forked by the row-norm gate (call_tag != 0) or by the
 // `fork` event, and joined by a device flag (T > 0) or the `join` event.
+// party: whose selection this is (see SelTurn).
 struct PathStreams {
   hipStream_t st;
   hipStream_t side;
   int call_tag;
   hipEvent_t fork, join;
+  int party;
 };
+
+// Held while a call is enqueued, by the context's entry points and by the
+// static one: two streams may share a hardware queue, where a wait for the
+// other call's turn must not come between that call's kernels.
+std::unique_lock<std::mutex> lock_enqueue();
 
 // Records the message gmc_last_error() returns; returns code.
 int set_error(int code, const char* fmt, ...);

@@ -563,7 +563,7 @@ __device__ __forceinline__ float next_threshold(float cut, float last_cut, int r
 constexpr int kResJ = 14;
 template <bool RES, int J, int R, int PF, bool AL = true, bool S = true>
 __device__ __forceinline__ void select_rounds(const Shape& sh, const Params& pr, const Ws& ws, int nblk,
-                                              const SelOut& so) {
+                                              const SelOut& so, const SelTurn& turn) {
   extern __shared__ __attribute__((aligned(16))) float dyn[];
   // LDS: b_m [mp] | alpha_m [mp] (AL, not with RES) | selected flags [N, padded to
   // 16 bytes] | the block's gains [tpb] | pool keys [N] (only when N exceeds
@@ -1195,6 +1195,7 @@ __device__ __forceinline__ void select_rounds(const Shape& sh, const Params& pr,
         st[5] = static_cast<float>(sh.rounds);
         st[6] = static_cast<float>(sh.m);
         st[7] = static_cast<float>(sh.N - sh.K);
+        problem_done(turn);
       }
       break;
     }
@@ -1203,29 +1204,36 @@ __device__ __forceinline__ void select_rounds(const Shape& sh, const Params& pr,
 
 // Streamed rows only.
 static __global__ void __launch_bounds__(256)
-select_stream_kernel(Shape sh, Params pr, Ws ws, int nblk, SelOut so) {
-  select_rounds<false, 0, 0, 4>(sh, pr, ws, nblk, so);
+select_stream_kernel(Shape sh, Params pr, Ws ws, int nblk, SelOut so, SelTurn turn) {
+  select_rounds<false, 0, 0, 4>(sh, pr, ws, nblk, so, turn);
 }
 // The same with the row weights read from memory, for more rows than both
 // arrays fit in LDS.
 static __global__ void __launch_bounds__(256)
-select_wide_kernel(Shape sh, Params pr, Ws ws, int nblk, SelOut so) {
-  select_rounds<false, 0, 0, 2, false>(sh, pr, ws, nblk, so);
+select_wide_kernel(Shape sh, Params pr, Ws ws, int nblk, SelOut so, SelTurn turn) {
+  select_rounds<false, 0, 0, 2, false>(sh, pr, ws, nblk, so, turn);
 }
 // Eight tokens per block, rows split over its waves.
 static __global__ void __launch_bounds__(256)
-select_split_kernel(Shape sh, Params pr, Ws ws, int nblk, SelOut so) {
-  select_rounds<true, 0, 0, 4>(sh, pr, ws, nblk, so);
+select_split_kernel(Shape sh, Params pr, Ws ws, int nblk, SelOut so, SelTurn turn) {
+  select_rounds<true, 0, 0, 4>(sh, pr, ws, nblk, so, turn);
 }
+// What a selection block may share a CU with (512 registers a SIMD lane, 160
+// KB of LDS): the gate block of the context's next call (its four waves, one
+// per SIMD, at most kGateRegs) and either a selection of the other entry point
+// (both then at most kHalfRegs, with LDS for both) or that call's waiting wave
+// (kWaitRegs; the block then at most kWholeRegs).  The resource tests hold the
+// built kernels to these.
+constexpr int kGateRegs = 24, kWaitRegs = 16, kHalfRegs = 240, kWholeRegs = 472;
+constexpr int kSelStaticLds = 23552, kHalfLds = 44 * 1024, kHalfLdsStatic = 112 * 1024;
+constexpr bool hold_half(int J, int R, bool S) { return !S && J * R <= 20; }
+
 // R tokens of up to 256 J client rows held per wave.  One wave per SIMD, so
-// up to 512 registers, but J R is kept near 75: the next call's gate block of
-// the bank stream waits beside this kernel, possibly on the same CU, and a
-// grid of one block per CU must still become resident (four waves of the
-// gate need 32 registers per SIMD; these kernels take at most 468 of 512).
+// up to 512 registers, but J R is kept near 75 (see kWholeRegs).
 template <int J, int R, bool S>
 static __global__ void __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(1, 1)))
-select_hold_kernel(Shape sh, Params pr, Ws ws, int nblk, SelOut so) {
-  select_rounds<false, J, R, 2, true, S>(sh, pr, ws, nblk, so);
+select_hold_kernel(Shape sh, Params pr, Ws ws, int nblk, SelOut so, SelTurn turn) {
+  select_rounds<false, J, R, 2, true, S>(sh, pr, ws, nblk, so, turn);
 }
 
 }  // namespace gmc

@@ -27,11 +27,13 @@ std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices] = {};
 
 // The call's workspace region starts cleared: earlier calls of another shape
-// left their data at other offsets.
-__global__ void __launch_bounds__(256) zero_fill_kernel(uint4* p, long long n16) {
+// left their data at other offsets.  Its first wave also takes the call's turn
+// on the device (here and not right before the selection: no launch for it).
+__global__ void __launch_bounds__(256) zero_fill_kernel(uint4* p, long long n16, gmc::SelTurn turn, int problems) {
   const long long stride = static_cast<long long>(gridDim.x) * blockDim.x;
   for (long long i = blockIdx.x * static_cast<long long>(blockDim.x) + threadIdx.x; i < n16; i += stride)
     p[i] = make_uint4(0u, 0u, 0u, 0u);
+  if (blockIdx.x == 0 && threadIdx.x == 0) gmc::take_turn(turn, problems);
 }
 
 }  // namespace
@@ -84,17 +86,24 @@ extern "C" int gmc_prune_static(const gmc_config* cfg, int64_t B, const void* hi
   }
   carve_workspace(c, static_cast<char*>(base), &ws);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  const auto enqueue = lock_enqueue();
+  SelTurn turn{nullptr, kPartyStatic};
   if (s.K < s.N) {
+    err = selection_turn(&turn.words);
+    if (err != hipSuccess) return set_error(GMC_ERR_HIP, "gmc_prune_static: turn words (%s)", hipGetErrorString(err));
     const long long n16 = static_cast<long long>(bytes / 16);
     const int blocks = static_cast<int>(std::min<long long>(1024, (n16 + 255) / 256));
-    hipLaunchKernelGGL(zero_fill_kernel, dim3(std::max(blocks, 1)), dim3(256), 0, st, static_cast<uint4*>(base), n16);
+    hipLaunchKernelGGL(zero_fill_kernel, dim3(std::max(blocks, 1)), dim3(256), 0, st, static_cast<uint4*>(base), n16,
+                       turn, s.B);
     err = hipGetLastError();
     if (err != hipSuccess) return set_error(GMC_ERR_HIP, "gmc_prune_static: clearing the scratch (%s)",
                                             hipGetErrorString(err));
   }
   const Params pr = params_of(c);
-  const PathStreams ps{st, nullptr, 0, nullptr, nullptr};
+  const PathStreams ps{st, nullptr, 0, nullptr, nullptr, kPartyStatic};
   bool cert = false;
-  return enqueue_prune(c, pr, ws, s, ps, 0, hidden, text_q, vis_k, pos3d, out_hidden, out_pos, out_idx, nonvis_lse,
-                       gmc_trace{}, &cert);
+  rc = enqueue_prune(c, pr, ws, s, ps, 0, hidden, text_q, vis_k, pos3d, out_hidden, out_pos, out_idx, nonvis_lse,
+                     gmc_trace{}, &cert);
+  if (rc != GMC_OK && turn.words) (void)launch_leave_turn(turn, st);
+  return rc;
 }

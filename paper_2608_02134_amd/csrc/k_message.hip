@@ -63,16 +63,18 @@ __global__ void __launch_bounds__(256) rownorm_kernel(Shape sh, Ws ws, const T* 
 // stream see the norms and the per-call reset, and start only after the
 // caller's stream has finished the previous call.  The caller may have queued
 // other work ahead of the call, so the wait is bounded in time (10 s of the
-// constant clock), not in polls; a timeout raises the sticky status bit.
+// constant clock), not in polls; a timeout raises the sticky status bit.  It
+// waits beside the previous call's selection, which counts on its registers
+// (kGateRegs): four flags in flight a thread, not eight.
 __global__ void __launch_bounds__(256) bank_gate_kernel(Shape sh, Ws ws, int call_tag) {
   const int nb = (sh.N + 3) / 4, total = nb * sh.B;
   const unsigned long long t0 = static_cast<unsigned long long>(wall_clock64());
   bool expired = false;
-  for (int x0 = 0; x0 < total && !expired; x0 += 256 * 8) {
-    int v[8];
-    bool need[8];
+  for (int x0 = 0; x0 < total && !expired; x0 += 256 * 4) {
+    int v[4];
+    bool need[4];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
+    for (int q = 0; q < 4; ++q) {
       const int x = x0 + q * 256 + static_cast<int>(threadIdx.x);
       need[q] = x < total;
       const int xc = min(x, total - 1), p = xc / nb, b = xc % nb;
@@ -81,7 +83,7 @@ __global__ void __launch_bounds__(256) bank_gate_kernel(Shape sh, Ws ws, int cal
     for (int spin = 0;; ++spin) {
       bool pend = false;
 #pragma unroll
-      for (int q = 0; q < 8; ++q) pend |= need[q] && v[q] != call_tag;
+      for (int q = 0; q < 4; ++q) pend |= need[q] && v[q] != call_tag;
       if (!pend) break;
       if ((spin & 255) == 255 && static_cast<unsigned long long>(wall_clock64()) - t0 > kGateWaitTicks) {
         raise_status(ws.cnt, kStatusBank);
@@ -90,7 +92,7 @@ __global__ void __launch_bounds__(256) bank_gate_kernel(Shape sh, Ws ws, int cal
       }
       __builtin_amdgcn_s_sleep(8);   // a light poll: it may wait through a whole selection
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
+      for (int q = 0; q < 4; ++q) {
         if (!need[q] || v[q] == call_tag) continue;
         const int x = x0 + q * 256 + static_cast<int>(threadIdx.x), p = x / nb, b = x % nb;
         v[q] = __hip_atomic_load(&ws.ftag[p * ws.s_ftag + b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -565,17 +565,18 @@ struct SelVariant {
   const void* fn;
   int J, R;            // rows / 256 and tokens per wave held in registers (0: none)
   bool streams;        // takes more tokens than the held ones
+  bool half;           // at most kHalfRegs registers
   int lds;             // dynamic LDS the occupancy below was asked for (-1: not yet)
   int per_cu;
 };
 enum { kSelStream, kSelWide, kSelSplit, kSelHold };   // g_sel: hold variants by J, then R
 static SelVariant g_sel[] = {
-    {reinterpret_cast<const void*>(select_stream_kernel), 0, 0, true, -1, 0},
-    {reinterpret_cast<const void*>(select_wide_kernel), 0, 0, true, -1, 0},
-    {reinterpret_cast<const void*>(select_split_kernel), 0, 0, false, -1, 0},
-#define GMC_HOLD(J, R)                                                               \
-  {reinterpret_cast<const void*>(select_hold_kernel<J, R, false>), J, R, false, -1, 0}, \
-  {reinterpret_cast<const void*>(select_hold_kernel<J, R, true>), J, R, true, -1, 0},
+    {reinterpret_cast<const void*>(select_stream_kernel), 0, 0, true, true, -1, 0},
+    {reinterpret_cast<const void*>(select_wide_kernel), 0, 0, true, true, -1, 0},
+    {reinterpret_cast<const void*>(select_split_kernel), 0, 0, false, true, -1, 0},
+#define GMC_HOLD(J, R)                                                                                          \
+  {reinterpret_cast<const void*>(select_hold_kernel<J, R, false>), J, R, false, hold_half(J, R, false), -1, 0}, \
+  {reinterpret_cast<const void*>(select_hold_kernel<J, R, true>), J, R, true, hold_half(J, R, true), -1, 0},
     GMC_HOLD(4, 5) GMC_HOLD(8, 5) GMC_HOLD(14, 3) GMC_HOLD(14, 5) GMC_HOLD(20, 2) GMC_HOLD(20, 3) GMC_HOLD(24, 3)
     GMC_HOLD(28, 2) GMC_HOLD(32, 2) GMC_HOLD(36, 2) GMC_HOLD(48, 1)
 #undef GMC_HOLD
@@ -608,17 +609,55 @@ static int variant_per_cu(SelVariant& v, size_t lds) {
   return v.per_cu;
 }
 
+// The turn words of every device.
+static __device__ int sel_turn_words[4];
+
+hipError_t selection_turn(int** words) {
+  static std::mutex mu;
+  static int* known[64] = {};
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess || dev < 0 || dev >= 64) return e != hipSuccess ? e : hipErrorInvalidDevice;
+  std::lock_guard<std::mutex> lk(mu);
+  if (!known[dev]) {
+    void* p = nullptr;
+    e = hipGetSymbolAddress(&p, HIP_SYMBOL(sel_turn_words));
+    if (e != hipSuccess) return e;
+    known[dev] = static_cast<int*>(p);
+  }
+  *words = known[dev];
+  return hipSuccess;
+}
+
+__global__ void __launch_bounds__(64) take_turn_kernel(SelTurn turn, int problems) {
+  if (threadIdx.x == 0) take_turn(turn, problems);
+}
+__global__ void __launch_bounds__(64) leave_turn_kernel(SelTurn turn) {
+  if (threadIdx.x == 0) leave_turn(turn);
+}
+hipError_t launch_leave_turn(const SelTurn& turn, hipStream_t st) {
+  hipLaunchKernelGGL(leave_turn_kernel, dim3(1), dim3(64), 0, st, turn);
+  return hipGetLastError();
+}
+
 struct SelPlan {
   const SelVariant* v = nullptr;   // null: the call does not qualify
   int nblk = 0;                    // blocks per problem
   size_t lds = 0;
+  bool turn = false;               // needs the device without another selection
 };
 
 // The persistent variant of a call: not with large pools or keys beyond LDS.
 // Per token the row-split kernel forms the sums in its own order; held and
 // streamed rows share another, so a shape keeps one result whichever of them
 // it takes.
-static SelPlan select_plan(const Shape& sh) {
+// Beside a selection of the other entry point (see SelTurn): half variants
+// with one block per CU, up to kHalfLds (context) and kHalfLdsStatic of LDS,
+// fit a CU side by side, with the gate of the context's next call.  The static
+// entry takes only these (what is larger runs round by round, with no waits
+// between blocks), so the common one-image calls of a context need no turn;
+// its other calls take one (one launch more: 1 to 6 us in calls of 450 to 1500).
+static SelPlan select_plan(const Shape& sh, int party) {
   SelPlan pl;
   if (sh.pool_cap > 64 || sh.N > kLdsKeys) return pl;
   std::lock_guard<std::mutex> lk(g_sel_mu);
@@ -633,7 +672,11 @@ static SelPlan select_plan(const Shape& sh) {
   auto full = [&](int blocks) { const int t = (sh.N + blocks - 1) / blocks; return (sh.N + t - 1) / t; };
   auto take = [&](SelVariant& v, int blocks, int per_cu) {
     const size_t lds = lds_of(v, blocks);
+    const bool half = v.half && blocks * sh.B <= g_n_cu &&
+                      lds + kSelStaticLds <= static_cast<size_t>(party == kPartyStatic ? kHalfLdsStatic : kHalfLds);
+    if (party == kPartyStatic && !half) return false;
     if (min(variant_per_cu(v, lds), per_cu) * g_n_cu < blocks * sh.B) return false;
+    pl.turn = !half;
     pl.v = &v;
     pl.nblk = blocks;
     pl.lds = lds;
@@ -669,9 +712,14 @@ static SelPlan select_plan(const Shape& sh) {
   return pl;
 }
 
-hipError_t launch_selection(const Shape& sh, const Params& pr, const Ws& ws, const SelOut& so, hipStream_t st,
-                            bool* support_ready) {
+hipError_t launch_selection(const Shape& sh, const Params& pr, const Ws& ws, const SelOut& so, int party,
+                            hipStream_t st, bool* support_ready) {
   *support_ready = false;
+  SelTurn turn{nullptr, party};
+  if (party == kPartyStatic) {
+    const hipError_t e = selection_turn(&turn.words);
+    if (e != hipSuccess) return e;
+  }
   if (sh.rounds == 0) {
     // the image seeds already fill the budget (K = I): only the objective;
     // the assignment builds the support list from the selection marks
@@ -680,18 +728,30 @@ hipError_t launch_selection(const Shape& sh, const Params& pr, const Ws& ws, con
     timer_mark(kStObjective, false, st);
     return hipGetLastError();
   }
-  if (const SelPlan pl = select_plan(sh); pl.v) {
+  if (const SelPlan pl = select_plan(sh, party); pl.v) {
     timer_mark(kStSelect, true, st);
+    if (party != kPartyStatic && pl.turn) {
+      const hipError_t e = selection_turn(&turn.words);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL(take_turn_kernel, dim3(1), dim3(64), 0, st, turn, sh.B);
+    }
     Shape a0 = sh;
     Params a1 = pr;
     Ws a2 = ws;
     int a3 = pl.nblk;
     SelOut a4 = so;
-    void* args[] = {&a0, &a1, &a2, &a3, &a4};
+    SelTurn a5 = turn;
+    void* args[] = {&a0, &a1, &a2, &a3, &a4, &a5};
     const hipError_t e = hipLaunchKernel(pl.v->fn, dim3(pl.nblk, sh.B), dim3(256), args, pl.lds, st);
+    if (e != hipSuccess && turn.words) (void)launch_leave_turn(turn, st);
     timer_mark(kStSelect, false, st);
     *support_ready = true;
     return e != hipSuccess ? e : hipGetLastError();
+  }
+  // round by round: no waits between blocks
+  if (turn.words) {
+    const hipError_t e = launch_leave_turn(turn, st);
+    if (e != hipSuccess) return e;
   }
   const bool global_keys = sh.N > kLdsKeys;
   const size_t key_lds = global_keys ? 0 : static_cast<size_t>(sh.N) * sizeof(uint32_t);
