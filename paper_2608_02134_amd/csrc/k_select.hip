@@ -27,6 +27,7 @@
 #include "gmc_device.h"
 #include "gmc_internal.h"
 #include "gmc_kernels.h"
+#include "gmc_occupancy.h"
 #include "gmc_select.h"
 
 namespace gmc {
@@ -566,26 +567,25 @@ struct SelVariant {
   int J, R;            // rows / 256 and tokens per wave held in registers (0: none)
   bool streams;        // takes more tokens than the held ones
   bool half;           // at most kHalfRegs registers
-  int lds;             // dynamic LDS the occupancy below was asked for (-1: not yet)
-  int per_cu;
+  KernelRoom room;
 };
 enum { kSelStream, kSelWide, kSelSplit, kSelHold };   // g_sel: hold variants by J, then R
 static SelVariant g_sel[] = {
-    {reinterpret_cast<const void*>(select_stream_kernel), 0, 0, true, true, -1, 0},
-    {reinterpret_cast<const void*>(select_wide_kernel), 0, 0, true, true, -1, 0},
-    {reinterpret_cast<const void*>(select_split_kernel), 0, 0, false, true, -1, 0},
+    {reinterpret_cast<const void*>(select_stream_kernel), 0, 0, true, true},
+    {reinterpret_cast<const void*>(select_wide_kernel), 0, 0, true, true},
+    {reinterpret_cast<const void*>(select_split_kernel), 0, 0, false, true},
 #define GMC_HOLD(J, R)                                                                                          \
-  {reinterpret_cast<const void*>(select_hold_kernel<J, R, false>), J, R, false, hold_half(J, R, false), -1, 0}, \
-  {reinterpret_cast<const void*>(select_hold_kernel<J, R, true>), J, R, true, hold_half(J, R, true), -1, 0},
+  {reinterpret_cast<const void*>(select_hold_kernel<J, R, false>), J, R, false, hold_half(J, R, false)}, \
+  {reinterpret_cast<const void*>(select_hold_kernel<J, R, true>), J, R, true, hold_half(J, R, true)},
     GMC_HOLD(4, 5) GMC_HOLD(8, 5) GMC_HOLD(14, 3) GMC_HOLD(14, 5) GMC_HOLD(20, 2) GMC_HOLD(20, 3) GMC_HOLD(24, 3)
     GMC_HOLD(28, 2) GMC_HOLD(32, 2) GMC_HOLD(36, 2) GMC_HOLD(48, 1)
 #undef GMC_HOLD
 };
-static std::mutex g_sel_mu;   // the static-scratch entry point runs beside the context's calls
+static std::mutex g_sel_mu;
 static int g_n_cu = -1, g_lds_max = 0;
 
-// Blocks of a variant that one CU holds at once, 0 if none (g_sel_mu held).
-static int variant_per_cu(SelVariant& v, size_t lds) {
+// The device's CUs and LDS per block, 0 CUs if unknown (g_sel_mu held).
+static int device_cus() {
   if (g_n_cu < 0) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
@@ -593,20 +593,23 @@ static int variant_per_cu(SelVariant& v, size_t lds) {
         hipDeviceGetAttribute(&g_lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
       g_n_cu = 0;
   }
-  if (g_n_cu <= 0 || lds > static_cast<size_t>(g_lds_max)) return 0;
-  if (v.lds != static_cast<int>(lds)) {
-    v.lds = static_cast<int>(lds);
-    v.per_cu = 0;
-    int n = 0;
-    // dynamic LDS above 64 KB has to be granted to the kernel first
-    if ((lds <= 64 * 1024 ||
-         hipFuncSetAttribute(v.fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)) == hipSuccess) &&
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, v.fn, 256, lds) == hipSuccess)
-      v.per_cu = n;
-    else
-      (void)hipGetLastError();   // too much LDS beside the static arrays: another variant is taken
-  }
-  return v.per_cu;
+  return g_n_cu;
+}
+
+// Blocks of a variant that one CU holds at once, 0 if none (g_sel_mu held).
+static int variant_per_cu(SelVariant& v, size_t lds) {
+  if (device_cus() <= 0 || lds > static_cast<size_t>(g_lds_max)) return 0;
+  // failures: too much LDS beside the static arrays, another variant is taken
+  auto ok = [](hipError_t e) {
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e == hipSuccess;
+  };
+  return v.room.blocks(
+      lds,
+      [&](size_t n) {
+        return ok(hipFuncSetAttribute(v.fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(n)));
+      },
+      [&](size_t n, int* blocks) { return ok(hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, v.fn, 256, n)); });
 }
 
 // The turn words of every device.
@@ -682,7 +685,7 @@ static SelPlan select_plan(const Shape& sh, int party) {
     pl.lds = lds;
     return true;
   };
-  if (variant_per_cu(g_sel[kSelStream], 0) < 1) return pl;
+  if (device_cus() < 1) return pl;
   // about two gain tokens per wave
   const int want = max((sh.N + 7) / 8, ((sh.m + 63) / 64 + 3) / 4);
   const int one = min(min(g_n_cu / sh.B, want), kMaxPersist);   // one block per CU
