@@ -569,16 +569,17 @@ struct SelVariant {
   bool half;           // at most kHalfRegs registers
   KernelRoom room;
 };
-enum { kSelStream, kSelWide, kSelSplit, kSelHold };   // g_sel: hold variants by J, then R
+enum { kSelStream, kSelWide, kSelSplit, kSelHold };   // g_sel: hold variants, each kind by J, then R
 static SelVariant g_sel[] = {
     {reinterpret_cast<const void*>(select_stream_kernel), 0, 0, true, true},
     {reinterpret_cast<const void*>(select_wide_kernel), 0, 0, true, true},
     {reinterpret_cast<const void*>(select_split_kernel), 0, 0, false, true},
-#define GMC_HOLD(J, R)                                                                                          \
-  {reinterpret_cast<const void*>(select_hold_kernel<J, R, false>), J, R, false, hold_half(J, R, false)}, \
-  {reinterpret_cast<const void*>(select_hold_kernel<J, R, true>), J, R, true, hold_half(J, R, true)},
-    GMC_HOLD(4, 5) GMC_HOLD(8, 5) GMC_HOLD(14, 3) GMC_HOLD(14, 5) GMC_HOLD(20, 2) GMC_HOLD(20, 3) GMC_HOLD(24, 3)
-    GMC_HOLD(28, 2) GMC_HOLD(32, 2) GMC_HOLD(36, 2) GMC_HOLD(48, 1)
+#define GMC_HOLD(J, R, S) {reinterpret_cast<const void*>(select_hold_kernel<J, R, S>), J, R, S, hold_half(J, R, S), {}},
+    GMC_HOLD(4, 5, false) GMC_HOLD(8, 5, false) GMC_HOLD(14, 3, false) GMC_HOLD(14, 5, false) GMC_HOLD(20, 2, false)
+    GMC_HOLD(20, 3, false) GMC_HOLD(24, 3, false) GMC_HOLD(28, 2, false) GMC_HOLD(32, 2, false) GMC_HOLD(36, 2, false)
+    GMC_HOLD(48, 1, false)
+    GMC_HOLD(4, 5, true) GMC_HOLD(8, 5, true) GMC_HOLD(14, 5, true) GMC_HOLD(20, 3, true) GMC_HOLD(24, 3, true)
+    GMC_HOLD(28, 2, true) GMC_HOLD(32, 2, true) GMC_HOLD(36, 2, true) GMC_HOLD(48, 1, true)
 #undef GMC_HOLD
 };
 static std::mutex g_sel_mu;
@@ -692,11 +693,7 @@ static SelPlan select_plan(const Shape& sh, int party) {
   if (one >= 1 && sh.N <= 8 * one && sh.m <= 256 * kResJ && take(g_sel[kSelSplit], (sh.N + 7) / 8, 1)) return pl;
   if (one >= 1) {
     // rows in registers: the narrowest variant the rows fit, of those the
-    // fewest tokens per wave that cover the block's, else the most.  Held
-    // rows win wherever they were measured (with all gains formed), from one
-    // image (M = 6944: 460 against 496 us per call; M = 4692, N = 2580: 767
-    // against 915; the document page 1673 against 1994) to sixteen (1271
-    // against 1296, 31 % of the tokens held).
+    // fewest tokens per wave that cover the block's, else the most.
     const int nblk = full(one), tokens = ((sh.N + nblk - 1) / nblk + 3) / 4;
     SelVariant* best = nullptr;
     for (int i = kSelHold; i < static_cast<int>(sizeof(g_sel) / sizeof(g_sel[0])); ++i) {
@@ -704,9 +701,27 @@ static SelPlan select_plan(const Shape& sh, int party) {
       if (256 * v.J < sh.m || v.streams != (tokens > v.R) || (best && (v.J > best->J || best->R >= tokens))) continue;
       best = &v;
     }
+    // With every token held they win wherever they were measured (us a call,
+    // held / streamed at two blocks per CU; 8 heads, d = 512 unless said):
+    // J = 4 137 / 159, 8 198 / 217, 14 191 / 208, 20 264 / 298, 24 292 / 326,
+    // 28 390 / 433, 32 330 / 383, 36 473 / 534, 48 372 / 390.  With some of
+    // them streamed, which one block per CU does with half the waves, they win
+    // up to 16 problems: J = 4 and 8 by 1 to 5 %, 14 (d = 3584, N = 1296) with 2
+    // problems 357 / 420, 4 507 / 561, 8 723 / 743; 20 466 / 488, 24 540 / 566,
+    // 28 726 / 750, 32 742 / 782 (the page 1489 / 1531), 36 914 / 951, 48 546 /
+    // 551 and 852 / 875 (but 407 / 403 with two tokens a wave).  They lose with
+    // more problems (32: J = 14 2256 / 2182, 20 1346 / 1304) and, where two
+    // streamed blocks fit a CU with ease (J <= 14), with less than two fifths
+    // of the tokens held (16 problems: J = 14 with 24 % 1148 / 1138, 8 with
+    // 33 % 524 / 511).
+    if (best && best->streams && (sh.B > 16 || (best->J <= 14 && 5 * best->R < 2 * tokens))) best = nullptr;
     if (best && take(*best, nblk, 1)) return pl;
   }
-  // streamed: two blocks per CU where they fit, twice the waves in flight
+  // streamed: two blocks per CU where they fit, twice the waves in flight.
+  // Beyond LDS for weights and coverage the weights come from memory: against
+  // the kernel that read them so for every M, M = 19152 1103 -> 1027 us a call
+  // (4 problems 1930 -> 1796), M = 23552, N = 4096 2458 -> 2018; the rounds as
+  // launches of their own take 1105, 1586 and 1883.
   for (const int i : {kSelStream, kSelWide})
     for (int per = 2; per >= 1; --per) {
       const int blocks = min(min(per * g_n_cu / sh.B, want), kMaxPersist);

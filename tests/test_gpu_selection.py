@@ -19,8 +19,8 @@ if not torch.cuda.is_available():
 
 # batch, grid (frames, h, w), queries, budget; 8 query heads, so M = 8 T + N + 256
 CASES = {
-    "rows_1024": (40, (1, 8, 13), 3, 40),            # J = 4, 6 blocks a problem
-    "rows_2048_streams_rest": (16, (1, 19, 21), 16, 40),   # J = 8, 25 tokens a block: 20 held
+    "rows_1024": (40, (1, 8, 13), 3, 40),            # M = 384, J = 4, 6 blocks a problem
+    "rows_2048_streams_rest": (16, (1, 19, 21), 16, 40),   # M = 783, J = 4, 25 tokens a block: 20 held
     "rows_3584_three": (8, (1, 15, 20), 200, 40),    # J = 14, R = 3
     "rows_3584_five": (12, (1, 15, 20), 200, 40),    # J = 14, R = 5
     "rows_5120_exact": (1, (1, 16, 24), 560, 60),    # J = 20, M = 5120
@@ -33,6 +33,19 @@ CASES = {
     "rows_12288": (2, (1, 10, 13), 1480, 33),        # J = 48
     "streamed": (2, (1, 11, 12), 1600, 33),          # M = 13188: weights and coverage in LDS
     "streamed_weights_in_memory": (2, (1, 9, 11), 2400, 33),   # M = 19555
+    "rows_1376_five": (16, (1, 16, 20), 100, 40),    # J = 8, every token held
+    # tokens beyond the held ones streamed
+    "rows_1497_and_streamed": (16, (1, 21, 21), 100, 40),   # J = 8, 28 tokens a block: 20 held
+    "rows_2297_and_streamed": (12, (1, 21, 21), 200, 40),   # J = 14, 21: 20
+    "rows_4676_and_streamed": (6, (1, 30, 34), 425, 40),    # J = 20, 25: 12
+    "rows_5456_and_streamed": (8, (1, 20, 20), 600, 40),    # J = 24, 13: 12
+    "rows_7056_and_streamed": (8, (1, 20, 20), 800, 40),    # J = 28, 13: 8
+    "rows_7856_and_streamed": (8, (1, 20, 20), 900, 40),    # J = 32, 13: 8
+    "rows_9056_and_streamed": (8, (1, 20, 20), 1050, 40),   # J = 36, 13: 8
+    "rows_11056_and_streamed": (2, (1, 20, 20), 1300, 40),  # J = 48, 8: 4
+    # all streamed: too few of the tokens would be held, too many problems
+    "few_held": (16, (1, 30, 30), 16, 40),           # M = 1284, 57 tokens a block
+    "seventeen_problems": (17, (1, 19, 21), 16, 40),
 }
 
 
