@@ -54,10 +54,13 @@ struct AudTile {
 
 // C consecutive elements (element-aligned addresses: the tensors may be views
 // at any element) as fp32 or as an MFMA fragment.
+template <typename T>
+using GlobalPtr = const __attribute__((address_space(1))) T*;
 template <typename T, int C>
-__device__ __forceinline__ void aud_load(const T* src, float (&v)[C]) {
+__device__ __forceinline__ void aud_load(GlobalPtr<T> src, float (&v)[C]) {
   struct __attribute__((packed, aligned(sizeof(T)))) Pack { T x[C]; };
-  const Pack pk = *reinterpret_cast<const Pack*>(src);
+  Pack pk;
+  __builtin_memcpy(&pk, (const T*)src, sizeof(pk));
 #pragma unroll
   for (int c = 0; c < C; ++c) v[c] = to_f32(pk.x[c]);
 }
@@ -74,6 +77,9 @@ __device__ __forceinline__ Frag<float> aud_frag(const float* src) {
   for (int c = 0; c < 8; ++c) f.v[c] = src[c];
   return f;
 }
+
+// A value row of zeros.
+static __device__ const float aud_zeros[256] = {};
 
 // One block's queries and its way over the rows of a [rows][Hkv][dh] tensor.
 template <typename T, int DH>
@@ -122,9 +128,12 @@ struct AudBlock {
     for (int e = 0; e < 4; ++e) acc[e] *= scale;
     return acc;
   }
-  // the lane's dims (DT of them, from DT (lane % 16)) of value row `row`
+  // the lane's dims (DT of them, from DT (lane % 16)) of value row `row`; past
+  // the end zeros (the attention there is zero, but another row loaded in its
+  // place may hold infinities)
   __device__ void values(const T* vb, int row, int rows, float (&v)[DT]) const {
-    aud_load<T, DT>(vb + min(row, rows - 1) * stride + r * DT, v);
+    GlobalPtr<T> src = row < rows ? (GlobalPtr<T>)(vb + row * stride) : (GlobalPtr<T>)aud_zeros;
+    aud_load<T, DT>(src + r * DT, v);
   }
 
   // log-sum-exp of the block's clients over the rows, with the nonvisual part;
@@ -149,19 +158,21 @@ struct AudBlock {
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         if (ct * 16 + 4 * kg + e < rows) nm = fmaxf(nm, s[e]);
-      if (nm == -INFINITY) continue;
-      float t = sm * __expf(mx - nm);
+      // (all -inf or NaN so far: the former add nothing, a NaN stays)
+      const float ref = nm == -INFINITY ? 0.f : nm;
+      float t = sm * __expf(mx - ref);
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        if (ct * 16 + 4 * kg + e < rows) t += __expf(s[e] - nm);
+        if (ct * 16 + 4 * kg + e < rows) t += __expf(s[e] - ref);
       sm = t;
       mx = nm;
     }
     }
-    // the four key groups of a client, then the waves in order
+    // the four key groups of a client, then the waves in order (without a
+    // finite logit a sum is zero or NaN)
     float gm = fmaxf(mx, xor_lane<16>(mx));
     gm = fmaxf(gm, xor_lane<32>(gm));
-    const float gs = add_xor32(add_xor16(mx == -INFINITY ? 0.f : sm * __expf(mx - gm)));
+    const float gs = add_xor32(add_xor16(mx == -INFINITY ? sm : sm * __expf(mx - gm)));
     if (lane < 16) { red_m[wave][lane] = gm; red_s[wave][lane] = gs; }
     __syncthreads();
     const int q = threadIdx.x;
@@ -169,7 +180,7 @@ struct AudBlock {
       float mm = -INFINITY;
       for (int w = 0; w < kAudW; ++w) mm = fmaxf(mm, red_m[w][q]);
       float s = 0.f;
-      for (int w = 0; w < kAudW; ++w) s += red_m[w][q] == -INFINITY ? 0.f : red_s[w][q] * __expf(red_m[w][q] - mm);
+      for (int w = 0; w < kAudW; ++w) s += red_m[w][q] == -INFINITY ? red_s[w][q] : red_s[w][q] * __expf(red_m[w][q] - mm);
       float D = mm + logf(s);
       if (nonvis && tl.valid(q)) {
         const float nv = nonvis[(static_cast<long long>(tl.p) * sh.hq + tl.head(sh, q)) * sh.T + tl.query(sh, q)];
