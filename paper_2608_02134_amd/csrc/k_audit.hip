@@ -128,6 +128,20 @@ struct AudBlock {
     for (int e = 0; e < 4; ++e) acc[e] *= scale;
     return acc;
   }
+  // the same from memory, two fragments at a time: for wide fp32 heads, whose
+  // queries and message sums leave no registers for a tile's keys
+  __device__ floatx4 logits_lean(const T* kb, int ct, int rows) const {
+    const T* kr = kb + min(ct * 16 + r, rows - 1) * stride + kg * 8;
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      acc = mma(aud_frag(kr + ks * 32), qf[ks], acc);
+      if (ks & 1) __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] *= scale;
+    return acc;
+  }
   // the lane's dims (DT of them, from DT (lane % 16)) of value row `row`; past
   // the end zeros (the attention there is zero, but another row loaded in its
   // place may hold infinities)
@@ -244,20 +258,32 @@ __global__ void __launch_bounds__(64 * kAudW) audit_full_kernel(Shape sh, AudWs 
     for (int e = 0; e < 4; ++e) ab.values(vb, min(ct, nt - 1) * 16 + 4 * ab.kg + e, sh.N, v2[b][e]);
     __builtin_amdgcn_sched_barrier(0);
   };
+  auto add = [&](int c0, int e, float s, const float (&v)[DT]) {
+    const bool ok = c0 + e < sh.N;
+    const float a = ok ? __expf(s - D) : 0.f;
+    if (ok && ab.rv) A[static_cast<long long>(c0 + e) * mg1] = a;
+#pragma unroll
+    for (int t = 0; t < DT; ++t) y[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[t], a, y[t], 0, 0, 0);
+  };
   auto step = [&](int ct, int b) {
-    const int c0 = ct * 16 + 4 * ab.kg;
-    const float (&v)[4][DT] = v2[b];
     const floatx4 s = ab.logits(kf[b]);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const bool ok = c0 + e < sh.N;
-      const float a = ok ? __expf(s[e] - D) : 0.f;
-      if (ok && ab.rv) A[static_cast<long long>(c0 + e) * mg1] = a;
-#pragma unroll
-      for (int t = 0; t < DT; ++t) y[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[e][t], a, y[t], 0, 0, 0);
-    }
+    for (int e = 0; e < 4; ++e) add(ct * 16 + 4 * ab.kg, e, s[e], v2[b][e]);
   };
-  if constexpr (sizeof(T) == 4 && DH > 128) {
+  if constexpr (sizeof(T) == 4 && DH > 224) {
+    // a tile's keys and values spill beside the queries and the message
+    for (int ct = ab.wave; ct < nt; ct += kAudW) {
+      const int c0 = ct * 16 + 4 * ab.kg;
+      const floatx4 s = ab.logits_lean(kb, ct, sh.N);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float v[DT];
+        ab.values(vb, c0 + e, sh.N, v);
+        add(c0, e, s[e], v);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  } else if constexpr (sizeof(T) == 4 && DH > 128) {
     // one tile's fragments fill the registers
     for (int ct = ab.wave; ct < nt; ct += kAudW) {
       load(ct, 0);
@@ -357,18 +383,32 @@ audit_compact_kernel(Shape sh, AudWs aw, const T* text_q, const T* comp_k, const
   const int nt = (sh.K + 15) / 16;
   for (int ct = ab.wave; ct < nt; ct += kAudW) {
     const int c0 = ct * 16 + 4 * ab.kg;
+    // wide fp32 heads: a tile's keys and values spill beside the queries and the
+    // two messages, so a value row is loaded when its turn comes, and above 192
+    // dims the keys too (8 heads, 1296 tokens, 256 carriers, 64 queries: 256 dims
+    // 223 -> 199 us an audit, 224 dims 173 -> 167)
+    constexpr bool kLean = sizeof(T) == 4 && DH > 160, kLeanKeys = kLean && DH > 192;
     float v[4][DT], mm[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      ab.values(vb, c0 + e, sh.K, v[e]);
+      if constexpr (!kLean) ab.values(vb, c0 + e, sh.K, v[e]);
       mm[e] = Mt[static_cast<long long>(min(c0 + e, sh.K - 1)) * mg1];
     }
-    Frag<T> kf[DH / 32];
-    ab.keys(kb, ct, sh.K, kf);
-    __builtin_amdgcn_sched_barrier(0);
-    const floatx4 s = ab.logits(kf);
+    floatx4 s;
+    if constexpr (kLeanKeys) {
+      s = ab.logits_lean(kb, ct, sh.K);
+    } else {
+      Frag<T> kf[DH / 32];
+      ab.keys(kb, ct, sh.K, kf);
+      __builtin_amdgcn_sched_barrier(0);
+      s = ab.logits(kf);
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
+      if constexpr (kLean) {
+        __builtin_amdgcn_sched_barrier(0);
+        ab.values(vb, c0 + e, sh.K, v[e]);
+      }
       const bool ok = c0 + e < sh.K && ab.rv;
       const float a = ok ? __expf(s[e] - D) : 0.f;
       mm[e] = ok ? mm[e] : 0.f;

@@ -32,6 +32,13 @@ def test_head_gram_keeps_its_registers(built):
     assert {n: k[".private_segment_fixed_size"] for n, k in found.items() if k[".private_segment_fixed_size"]} == {}
 
 
+def test_audit_keeps_its_registers(built):
+    """No head dimension (32..256) spills to scratch, in either type."""
+    found = _find(built, r"audit_(full|compact)_kernel")
+    assert len(found) == 32
+    assert {n: k[".private_segment_fixed_size"] for n, k in found.items() if k[".private_segment_fixed_size"]} == {}
+
+
 # --- selections that run side by side ----------------------------------------------
 # A selection's blocks wait for each other.  Two may be in flight on a device:
 # one of the context, one of the static entry point.
