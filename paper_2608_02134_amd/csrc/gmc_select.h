@@ -1,6 +1,6 @@
-// Device code of the batched responsibility selection shared by its
-// translation units: deterministic top-k, the batch pick, the butterfly
-// transpose-reduction and the persistent selection kernel.
+// Device code of the batched responsibility selection (included by
+// k_select.hip alone: its kernels are static): deterministic top-k, the batch
+// pick, the butterfly transpose-reduction and the persistent selection kernels.
 #pragma once
 
 #include <type_traits>

@@ -43,7 +43,7 @@ struct CosEpi {
   Ws ws;
   int ldK;
   float norm_eps;
-  static constexpr bool kRowStats = false, kStore4 = false;
+  static constexpr bool kRowStats = false;
   __device__ float row_scale(int p, int r) const {
     return 1.f / fmaxf(sqrtf(ws.n2[p * ws.s_n + r]), norm_eps);
   }
