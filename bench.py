@@ -58,23 +58,24 @@ def source_hash(paths=TRAFFIC_SOURCES) -> str:
 
 def stored_traffic(workload: str, stage: str):
     """HBM bytes per launch of the dominant kernel from the stored rocprofv3
-    FETCH_SIZE / WRITE_SIZE passes, scaled by the copy-kernel calibration;
-    None when absent or taken on different kernel sources."""
+    FETCH_SIZE / WRITE_SIZE passes, scaled by the copy-kernel calibration
+    (None when absent or taken on different kernel sources), a note on it and
+    the kernel's name."""
     try:
         with open(TRAFFIC_FILE) as f:
             rec = json.load(f)
     except (OSError, ValueError):
-        return None, "no stored counter measurement"
+        return None, "no stored counter measurement", None
     ent = rec.get("workloads", {}).get(workload)
     if not ent or ent.get("stage") != stage:
-        return None, "no stored counter measurement for this kernel"
+        return None, "no stored counter measurement for this kernel", None
     if ent.get("source_hash") != source_hash():
-        return None, "kernel sources changed since the counters were taken"
+        return None, "kernel sources changed since the counters were taken", ent["kernel"]
     cal = rec["copy_calibration"]
     fetch = ent["fetch_kib_per_launch"] * 1024.0 * cal["fetch_factor"]
     write = ent["write_kib_per_launch"] * 1024.0 * cal["write_factor"]
     return fetch + write, (f"rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE on {ent['kernel']}, "
-                           f"scaled by a {cal['bytes'] / 2**20:.0f} MiB copy; see profiles/")
+                           f"scaled by a {cal['bytes'] / 2**20:.0f} MiB copy; see profiles/"), ent["kernel"]
 
 
 def copy_calibration(mib: int, reps: int = 10):
@@ -111,6 +112,41 @@ def kernel_work(stage: str, w, m_rows: int, kr: int = 0, bsel: int = 16, pool_ca
     if stage == "logits":      # write the grounded client rows
         return "hbm", b * 4.0 * w.hq * w.t * n
     return None, None
+
+
+def roofline_of(stage, bound, work, avg_s, dtype, traffic, kernel, client_bytes):
+    """achieved, peak, unit, frac and what they count, for one launch of a stage.
+
+    The selection's algorithmic bytes (every candidate's row in every round) are
+    more than its kernels read: rows held in registers are read once per launch
+    and gains that cannot enter the pool are not formed.  Its achieved bandwidth
+    is what the counters saw, or, without a stored measurement, the client
+    matrix once; the algorithmic figure is given beside it."""
+    if bound != "hbm":
+        achieved = work / avg_s / 1e12
+        peak = BF16_PEAK_TFLOPS if dtype == "bf16" else FP32_PEAK_TFLOPS
+        return {"achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak}
+    r = {"achieved": work / avg_s / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s"}
+    if stage == "select":
+        r["algorithmic_gbs"] = r["achieved"]
+        r["achieved"] = (traffic or client_bytes) / avg_s / 1e9
+        r["achieved_counts"] = "measured traffic" if traffic else "the client matrix read once"
+    r["frac"] = r["achieved"] / r["peak"]
+    if traffic:
+        r["traffic_gbs"] = traffic / avg_s / 1e9
+        r["traffic_over_work"] = traffic / work
+        bw = r["traffic_gbs"] >= 0.5 * r["peak"]
+        if stage == "select":
+            how = {"select_split_kernel": "every client row held in registers and read once per launch",
+                   "select_hold_kernel": "client rows held in registers as far as they fit, the others' gains formed "
+                                         "only where they can enter the pool",
+                   "select_stream_kernel": "client rows streamed where their gains can enter the pool",
+                   "select_wide_kernel": "client rows streamed where their gains can enter the pool"}
+            r["regime"] = ("bandwidth: " if bw else "latency of the rounds' hand-offs: ") + how.get(kernel, "")
+        else:
+            r["regime"] = ("latency: operands cache-resident, measured traffic well below the algorithmic bytes"
+                           if traffic < 0.5 * work else "bandwidth: operands streamed past the L2 caches every round")
+    return r
 
 
 def main():
@@ -218,26 +254,10 @@ def main():
     dom = max(single_kernel, key=lambda s: stages[s]["ms_per_step"])
     bound, work = kernel_work(dom, w, m_rows, kr, bcap, pool_cap)
     avg_s = stages[dom]["launch_avg_us"] / 1e6
-    if bound == "hbm":
-        achieved, peak, unit = work / avg_s / 1e9, HBM_PEAK_GBS, "GB/s"
-    else:
-        achieved = work / avg_s / 1e12
-        peak = BF16_PEAK_TFLOPS if w.dtype == "bf16" else FP32_PEAK_TFLOPS
-        unit = "TFLOP/s"
-    traffic, traffic_note = stored_traffic(args.workload, dom)
-    roofline = {"bound": bound, "kernel": dom, "achieved": achieved, "peak": peak, "unit": unit,
-                "frac": achieved / peak, "traffic": traffic, "traffic_note": traffic_note,
-                "work_per_launch": work, "launch_avg_us": stages[dom]["launch_avg_us"],
-                "source_hash": source_hash()}
-    if bound == "hbm" and traffic:
-        # `achieved` counts the algorithmic bytes; the counters give what
-        # actually crossed the fabric.  Far fewer measured bytes than
-        # algorithmic ones means the kernel's operands stayed in the caches
-        # and its time is set by latency, not by HBM bandwidth.
-        roofline["traffic_gbs"] = traffic / avg_s / 1e9
-        roofline["traffic_over_work"] = traffic / work
-        roofline["regime"] = ("latency: operands cache-resident, measured traffic well below the algorithmic bytes"
-                              if traffic < 0.5 * work else "bandwidth: operands streamed past the L2 caches every round")
+    traffic, traffic_note, kernel = stored_traffic(args.workload, dom)
+    roofline = {"bound": bound, "kernel": dom, "traffic": traffic, "traffic_note": traffic_note,
+                "work_per_launch": work, "launch_avg_us": stages[dom]["launch_avg_us"], "source_hash": source_hash()}
+    roofline.update(roofline_of(dom, bound, work, avg_s, w.dtype, traffic, kernel, 4.0 * w.batch * w.n * m_rows))
 
     cpu = None
     if args.cpu_seconds > 0:

@@ -747,12 +747,12 @@ hipError_t launch_selection(const Shape& sh, const Params& pr, const Ws& ws, con
     return hipGetLastError();
   }
   if (const SelPlan pl = select_plan(sh, party); pl.v) {
-    timer_mark(kStSelect, true, st);
     if (party != kPartyStatic && pl.turn) {
       const hipError_t e = selection_turn(&turn.words);
       if (e != hipSuccess) return e;
       hipLaunchKernelGGL(take_turn_kernel, dim3(1), dim3(64), 0, st, turn, sh.B);
     }
+    timer_mark(kStSelect, true, st);
     Shape a0 = sh;
     Params a1 = pr;
     Ws a2 = ws;
