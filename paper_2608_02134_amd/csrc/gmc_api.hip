@@ -762,11 +762,26 @@ int enqueue_prune(const gmc_config& cfg, const Params& pr0, const Ws& ws, const 
     err = hipEventRecord(ps.join, ps.side);
     if (err != hipSuccess) return fail(GMC_ERR_HIP, "stream join: %s", hipGetErrorString(err));
   }
-  err = launch_message(s, pr, ws, views, tr.omega, flag_join ? bank_flag : nullptr, st);
+  // the turn of a context's selection that needs one is taken once nothing of
+  // the other stream is left to wait for: at the end of the last message
+  // kernel, or without text queries after the join (a static call has its turn
+  // already)
+  SelTurn turn = ps.turn;
+  const bool take = turn.party == kPartyContext && selection_needs_turn(s);
+  if (take) {
+    err = selection_turn(&turn.words);
+    if (err != hipSuccess) return fail(GMC_ERR_HIP, "turn words: %s", hipGetErrorString(err));
+  }
+  const SelTurn in_message{take && s.T > 0 ? turn.words : nullptr, turn.party};
+  err = launch_message(s, pr, ws, views, tr.omega, flag_join ? bank_flag : nullptr, in_message, st);
   if (err != hipSuccess) return fail(GMC_ERR_HIP, "message kernels: %s", hipGetErrorString(err));
   if (fork && !flag_join) {
     err = hipStreamWaitEvent(st, ps.join, 0);
     if (err != hipSuccess) return fail(GMC_ERR_HIP, "stream join: %s", hipGetErrorString(err));
+  }
+  if (take && s.T == 0) {
+    err = launch_take_turn(turn, s.B, st);
+    if (err != hipSuccess) return fail(GMC_ERR_HIP, "selection's turn: %s", hipGetErrorString(err));
   }
   // per-round outputs of the selection: the trace's buffers, completed with
   // the workspace's certificate buffers when the certificate is computed
@@ -782,10 +797,11 @@ int enqueue_prune(const gmc_config& cfg, const Params& pr0, const Ws& ws, const 
   if (s.nimg > 1) {
     // S_0: the largest singleton gain of every image (after the banks joined)
     err = launch_image_seeds(s, ws, st);
+    if (err != hipSuccess && turn.words) (void)launch_leave_turn(turn, st);
     if (err != hipSuccess) return fail(GMC_ERR_HIP, "image seeds: %s", hipGetErrorString(err));
   }
   bool support_ready = false;
-  err = launch_selection(s, pr, ws, so, ps.party, st, &support_ready);
+  err = launch_selection(s, pr, ws, so, turn, st, &support_ready);
   if (err != hipSuccess) return fail(GMC_ERR_HIP, "selection kernels: %s", hipGetErrorString(err));
   err = launch_assignment(s, pr, ws, hidden, support_ready, tr.assign, st);
   if (err != hipSuccess) return fail(GMC_ERR_HIP, "assignment kernels: %s", hipGetErrorString(err));
@@ -845,7 +861,7 @@ int run(int64_t B, const void* hidden, const void* text_q, const void* vis_k, co
   c.last_cert = false;
   // stage timing keeps every kernel on the caller's stream, so each stage's
   // span measures that stage alone
-  PathStreams ps{st, g_timer.on ? nullptr : c.side, 0, c.fork, c.join, kPartyContext};
+  PathStreams ps{st, g_timer.on ? nullptr : c.side, 0, c.fork, c.join, {nullptr, kPartyContext}};
   if (ps.side && s.B == 1 && s.K < s.N) {
     c.call_tag = c.call_tag == 0x7fffffff ? 1 : c.call_tag + 1;
     ps.call_tag = c.call_tag;

@@ -157,9 +157,10 @@ struct SelOut {
 // context (its calls run one after another) and one of the static entry point
 // (its calls must not overlap).  Either both fit (see select_plan), or the
 // context's takes a turn on the device: a word that a static call holds from
-// its first kernel to the end of its selection, and such a context call during
-// its selection.  Single waves of few registers wait (kWaitRegs), which leaves
-// the holder's grid room on their CU, and the holder never waits for the other.
+// its first kernel to the end of its selection, and such a context call from
+// the end of its last message kernel.  Single waves wait, which leave the
+// holder's grid room on their CU (see kHalfRegs), and the holder never waits
+// for the other.
 // The waits are bounded (2 s); a call that waited in vain takes the turn, and
 // its selection's own bounded waits note a grid that never became resident.
 // The words work under graph replay too, where the host has no part.

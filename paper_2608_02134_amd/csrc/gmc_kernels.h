@@ -39,9 +39,9 @@ struct MsgView {
 // the current one, sh.nviews in all), head weights over the views' patterns,
 // grounded row weights and the current view's energy (after launch_rownorm).
 // With bank_flag set (T > 0), the last kernel also waits until the flag
-// reads 1.
+// reads 1; with turn.words set (T > 0) it then takes the selection's turn.
 hipError_t launch_message(const Shape& sh, const Params& pr, const Ws& ws, const MsgView* views,
-                          float* trace_omega, const int* bank_flag, hipStream_t st);
+                          float* trace_omega, const int* bank_flag, const SelTurn& turn, hipStream_t st);
 
 // Sets *flag = 1 once the work before it on st has finished.
 hipError_t launch_bank_signal(int* flag, hipStream_t st);
@@ -53,14 +53,18 @@ hipError_t launch_banks(const Shape& sh, const Params& pr, const Ws& ws, const v
 // All selection rounds, then the final coverage and objective values.
 // *support_ready reports that the support list and slots were written too.
 // `so` receives each round's pool, batch, gains and pool scores (any may be
-// NULL).  party: whose call this is (see SelTurn); a static call's turn, taken
-// by its first kernel, is left here.
-hipError_t launch_selection(const Shape& sh, const Params& pr, const Ws& ws, const SelOut& so, int party,
+// NULL).  turn: whose call this is and the turn it has taken, if any, which is
+// left here.
+hipError_t launch_selection(const Shape& sh, const Params& pr, const Ws& ws, const SelOut& so, const SelTurn& turn,
                             hipStream_t st, bool* support_ready);
+
+// Whether a context's selection has to take a turn (see SelTurn).
+bool selection_needs_turn(const Shape& sh);
 
 // The current device's turn words.
 hipError_t selection_turn(int** words);
-// Leaves a turn, if this party holds it.
+// Takes a turn for a selection of `problems`; leaves one, if this party holds it.
+hipError_t launch_take_turn(const SelTurn& turn, int problems, hipStream_t st);
 hipError_t launch_leave_turn(const SelTurn& turn, hipStream_t st);
 
 // Certificate of the selection rounds from the exported per-round pools,

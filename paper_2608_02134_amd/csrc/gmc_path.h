@@ -21,13 +21,13 @@ struct Limits {
 // Streams of one call: everything runs on `st`; with `side` set the bank
 // kernels run there, forked by the row-norm gate (call_tag != 0) or by the
 // `fork` event, and joined by a device flag (T > 0) or the `join` event.
-// party: whose selection this is (see SelTurn).
+// turn: whose selection this is, and a static call's turn words.
 struct PathStreams {
   hipStream_t st;
   hipStream_t side;
   int call_tag;
   hipEvent_t fork, join;
-  int party;
+  SelTurn turn;
 };
 
 // Held while a call is enqueued, by the context's entry points and by the

@@ -1221,9 +1221,11 @@ select_split_kernel(Shape sh, Params pr, Ws ws, int nblk, SelOut so, SelTurn tur
 // What a selection block may share a CU with (512 registers a SIMD lane, 160
 // KB of LDS): the gate block of the context's next call (its four waves, one
 // per SIMD, at most kGateRegs) and either a selection of the other entry point
-// (both then at most kHalfRegs, with LDS for both) or that call's waiting wave
-// (kWaitRegs; the block then at most kWholeRegs).  The resource tests hold the
-// built kernels to these.
+// (both then at most kHalfRegs, with LDS for both) or a wave of that entry point
+// that waits for its turn: the static call's first kernel (kWaitRegs, beside at
+// most kWholeRegs) or the context's last message kernel (beside a static
+// selection, at most kHalfRegs and kHalfLdsStatic).  The resource tests hold
+// the built kernels to these.
 constexpr int kGateRegs = 24, kWaitRegs = 16, kHalfRegs = 240, kWholeRegs = 472;
 constexpr int kSelStaticLds = 23552, kHalfLds = 44 * 1024, kHalfLdsStatic = 112 * 1024;
 constexpr bool hold_half(int J, int R, bool S) { return !S && J * R <= 20; }

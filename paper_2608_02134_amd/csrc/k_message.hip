@@ -1189,7 +1189,7 @@ constexpr int kClusterThreads = 512;
 constexpr int kClusterGB = 16;   // block partial quads in flight per thread (more spills to scratch)
 
 __global__ void __launch_bounds__(kClusterThreads) __attribute__((amdgpu_waves_per_eu(1, 2)))
-cluster_kernel(Shape sh, Params pr, Ws ws, float* trace_omega, const int* bank_flag) {
+cluster_kernel(Shape sh, Params pr, Ws ws, float* trace_omega, const int* bank_flag, SelTurn turn) {
   constexpr int NT = kClusterThreads, kRW = 4;
   __shared__ float gam[kMaxHeads][kMaxHeads + 1];    // pattern Gram over the views
   __shared__ float cosm[kMaxHeads][kMaxHeads + 1];   // one view's Gamma, then the cosines
@@ -1409,6 +1409,8 @@ cluster_kernel(Shape sh, Params pr, Ws ws, float* trace_omega, const int* bank_f
       __builtin_amdgcn_s_sleep(2);
     }
   }
+  // the selection's turn (a launch of its own before the selection took 3 us)
+  if (turn.words && p == 0 && tid == 0) take_turn(turn, sh.B);
 }
 
 // Empty grounded bank (T = 0): omega = 0 and uniform energy ebar = 1.
@@ -1543,7 +1545,7 @@ static hipError_t message_view(const Shape& sv, const Params& pr, const Ws& wv, 
 
 template <typename T>
 static hipError_t message_impl(const Shape& sh, const Params& pr, const Ws& ws, const MsgView* views,
-                               float* trace_omega, const int* bank_flag, hipStream_t st) {
+                               float* trace_omega, const int* bank_flag, const SelTurn& turn, hipStream_t st) {
   if (sh.T == 0) {
     // no grounded rows: the value probe is not needed either
     timer_mark(kStHeads, true, st);
@@ -1569,7 +1571,8 @@ static hipError_t message_impl(const Shape& sh, const Params& pr, const Ws& ws, 
     if (err != hipSuccess) return err;
   }
   timer_mark(kStHeads, true, st);
-  hipLaunchKernelGGL(cluster_kernel, dim3(sh.B), dim3(kClusterThreads), 0, st, sh, pr, ws, trace_omega, bank_flag);
+  hipLaunchKernelGGL(cluster_kernel, dim3(sh.B), dim3(kClusterThreads), 0, st, sh, pr, ws, trace_omega, bank_flag,
+                     turn);
   timer_mark(kStHeads, false, st);
   return hipGetLastError();
 }
@@ -1592,9 +1595,9 @@ hipError_t launch_bank_gate(const Shape& sh, const Ws& ws, int call_tag, hipStre
 }
 
 hipError_t launch_message(const Shape& sh, const Params& pr, const Ws& ws, const MsgView* views,
-                          float* trace_omega, const int* bank_flag, hipStream_t st) {
-  if (sh.dtype == 0) return message_impl<float>(sh, pr, ws, views, trace_omega, bank_flag, st);
-  return message_impl<bf16_t>(sh, pr, ws, views, trace_omega, bank_flag, st);
+                          float* trace_omega, const int* bank_flag, const SelTurn& turn, hipStream_t st) {
+  if (sh.dtype == 0) return message_impl<float>(sh, pr, ws, views, trace_omega, bank_flag, turn, st);
+  return message_impl<bf16_t>(sh, pr, ws, views, trace_omega, bank_flag, turn, st);
 }
 
 hipError_t launch_bank_signal(int* flag, hipStream_t st) {

@@ -636,6 +636,10 @@ hipError_t selection_turn(int** words) {
 __global__ void __launch_bounds__(64) take_turn_kernel(SelTurn turn, int problems) {
   if (threadIdx.x == 0) take_turn(turn, problems);
 }
+hipError_t launch_take_turn(const SelTurn& turn, int problems, hipStream_t st) {
+  hipLaunchKernelGGL(take_turn_kernel, dim3(1), dim3(64), 0, st, turn, problems);
+  return hipGetLastError();
+}
 __global__ void __launch_bounds__(64) leave_turn_kernel(SelTurn turn) {
   if (threadIdx.x == 0) leave_turn(turn);
 }
@@ -660,7 +664,7 @@ struct SelPlan {
 // fit a CU side by side, with the gate of the context's next call.  The static
 // entry takes only these (what is larger runs round by round, with no waits
 // between blocks), so the common one-image calls of a context need no turn;
-// its other calls take one (one launch more: 1 to 6 us in calls of 450 to 1500).
+// its other calls take one.
 static SelPlan select_plan(const Shape& sh, int party) {
   SelPlan pl;
   if (sh.pool_cap > 64 || sh.N > kLdsKeys) return pl;
@@ -730,14 +734,13 @@ static SelPlan select_plan(const Shape& sh, int party) {
   return pl;
 }
 
-hipError_t launch_selection(const Shape& sh, const Params& pr, const Ws& ws, const SelOut& so, int party,
+bool selection_needs_turn(const Shape& sh) {
+  return sh.rounds > 0 && select_plan(sh, kPartyContext).turn;
+}
+
+hipError_t launch_selection(const Shape& sh, const Params& pr, const Ws& ws, const SelOut& so, const SelTurn& turn,
                             hipStream_t st, bool* support_ready) {
   *support_ready = false;
-  SelTurn turn{nullptr, party};
-  if (party == kPartyStatic) {
-    const hipError_t e = selection_turn(&turn.words);
-    if (e != hipSuccess) return e;
-  }
   if (sh.rounds == 0) {
     // the image seeds already fill the budget (K = I): only the objective;
     // the assignment builds the support list from the selection marks
@@ -746,12 +749,7 @@ hipError_t launch_selection(const Shape& sh, const Params& pr, const Ws& ws, con
     timer_mark(kStObjective, false, st);
     return hipGetLastError();
   }
-  if (const SelPlan pl = select_plan(sh, party); pl.v) {
-    if (party != kPartyStatic && pl.turn) {
-      const hipError_t e = selection_turn(&turn.words);
-      if (e != hipSuccess) return e;
-      hipLaunchKernelGGL(take_turn_kernel, dim3(1), dim3(64), 0, st, turn, sh.B);
-    }
+  if (const SelPlan pl = select_plan(sh, turn.party); pl.v) {
     timer_mark(kStSelect, true, st);
     Shape a0 = sh;
     Params a1 = pr;

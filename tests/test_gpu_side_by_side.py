@@ -44,7 +44,8 @@ def _same(got, want):
 
 
 @pytest.mark.parametrize("replayed", [False, True], ids=["eager", "graph"])
-@pytest.mark.parametrize("batch,grid,t", [(1, (1, 16, 24), 560), (8, (1, 15, 20), 200), (16, (1, 19, 21), 16)])
+@pytest.mark.parametrize("batch,grid,t", [(1, (1, 16, 24), 560), (8, (1, 15, 20), 200), (16, (1, 19, 21), 16),
+                                          (16, (1, 19, 21), 0)])
 def test_context_and_static_calls_side_by_side(batch, grid, t, replayed):
     ctx = synth.make_problem("tiny", batch=batch, grid=grid, t=t, k=60)
     sta = synth.make_problem("tiny", grid=(1, 24, 25), t=24, k=120)

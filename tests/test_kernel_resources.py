@@ -68,6 +68,9 @@ def _variants(built):
 def test_selection_blocks_leave_the_room_they_count_on(built, limits):
     gate, = _find(built, r"bank_gate_kernel").values()
     assert _regs(gate) <= limits["kGateRegs"] and gate[".group_segment_fixed_size"] == 0
+    cluster, = _find(built, r"cluster_kernel").values()
+    assert _regs(cluster) + limits["kHalfRegs"] + limits["kGateRegs"] <= CU_REGS
+    assert cluster[".group_segment_fixed_size"] + limits["kHalfLdsStatic"] <= CU_LDS
     for k in _find(built, r"take_turn_kernel|zero_fill_kernel").values():
         assert _regs(k) <= limits["kWaitRegs"] and k[".group_segment_fixed_size"] == 0
     assert limits["kWholeRegs"] + limits["kGateRegs"] + limits["kWaitRegs"] <= CU_REGS
