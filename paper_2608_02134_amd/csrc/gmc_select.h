@@ -314,10 +314,9 @@ __device__ __forceinline__ float transpose_reduce64(float* v, int lane) {
 // round:
 //   gains  - u_i of the block's tokens that may enter the pool, from client
 //            rows held in registers for the whole call or streamed from the
-//            caches; the block's
-//            gains are published together (0 for the other tokens), tagged
-//            with the pass over them (a round has a second one if the first
-//            left out too many)
+//            caches; the block's gains are published together (0 for the
+//            other tokens), tagged with the pass over them (a round has a
+//            second one if the first left out too many)
 //   pool   - every block that owns a row chunk (and the last block) waits
 //            for the tagged gains and picks the same pool (identical inputs,
 //            deterministic top-k)
