@@ -579,7 +579,10 @@ int make_shape(const Context& c, int64_t B, int64_t N, int64_t T, int64_t K_req,
 
 namespace gmc {
 
-std::unique_lock<std::mutex> lock_enqueue() { return std::unique_lock<std::mutex>(g_mu); }
+std::unique_lock<std::mutex> lock_enqueue() {
+  static std::mutex mu;   // not g_mu, under which other entry points synchronise
+  return std::unique_lock<std::mutex>(mu);
+}
 
 int resolve_shape(const gmc_config& g, const Limits& cap, int64_t B, int64_t N, int64_t T, int64_t K_req,
                   Shape* out, int64_t n_hist, int64_t n_images) {
@@ -867,6 +870,7 @@ int run(int64_t B, const void* hidden, const void* text_q, const void* vis_k, co
     ps.call_tag = c.call_tag;
   }
   bool cert = false;
+  const auto enqueue = lock_enqueue();
   rc = enqueue_prune(c.cfg, c.pr, c.ws, s, ps, c.diag, hidden, text_q, vis_k, pos3d, out_hidden, out_pos, out_idx,
                      nonvis_lse, tr, &cert, hist, image_id);
   c.last_cert = cert;

@@ -30,8 +30,8 @@ struct PathStreams {
   SelTurn turn;
 };
 
-// Held while a call is enqueued, by the context's entry points and by the
-// static one: two streams may share a hardware queue, where a wait for the
+// Held while a pruning call is enqueued, by the context's entry points and by
+// the static one: two streams may share a hardware queue, where a wait for the
 // other call's turn must not come between that call's kernels.
 std::unique_lock<std::mutex> lock_enqueue();
 

@@ -534,7 +534,7 @@ __device__ __forceinline__ void stream_gains(const float* const (&row)[T], const
 // The first round, and a call that traces its gains, form all; so do the
 // kernels whose blocks hold all their tokens, as a wave forms the held ones
 // together: with some left out nothing is saved and the rounds that go again
-// are lost (M = 6944: 458 us a call with all gains, 482 so; M = 4692,
+// are lost (M = 6928: 458 us a call with all gains, 482 so; M = 4692,
 // N = 2580: 769 and 810).
 // theta lies below the smallest gain of the last pool by twice the part that
 // this fell by in the last round: of the document page's 52 rounds 4 go again
@@ -556,7 +556,7 @@ __device__ __forceinline__ float next_threshold(float cut, float last_cut, int r
 // then read only the coverage.
 // R > 0: the rows of each wave's first R tokens stay in registers, up to 256 J
 // rows each; a round's gains read weights and coverage from LDS (measured at
-// M = 6944, two tokens a wave: 2.2 us of gains a round, 12 us streamed).
+// M = 6928, two tokens a wave: 2.2 us of gains a round, 12 us streamed).
 // Tokens beyond them, or all with R = 0, are streamed from the caches (S; not
 // S: the block has at most 4 R tokens).
 constexpr int kResJ = 14;
