@@ -3,6 +3,7 @@ bits it gives alone.  The context's selections here need the device to
 themselves (rows held in registers, one and several problems), so they and the
 static calls, launched eagerly or replayed from a graph, take turns."""
 import threading
+import time
 
 import pytest
 
@@ -108,5 +109,49 @@ def test_context_and_static_calls_side_by_side(batch, grid, t, replayed):
         assert len(got_c) == len(got_s) == CALLS
         assert all(_same(g, want_c) for g in got_c)
         assert all(_same(g, want_s) for g in got_s)
+    finally:
+        pr.close()
+
+
+@pytest.mark.parametrize("batch,grid,t", [(1, (1, 24, 25), 24), (1, (1, 46, 47), 64), (1, (1, 16, 24), 560),
+                                          (1, (1, 9, 11), 2400), (1, (1, 9, 11), 3200), (300, (1, 8, 8), 8)],
+                         ids=["split", "streamed", "streamed_rows", "weights_in_memory", "rounds", "rounds_many"])
+def test_static_routes_leave_their_turn(batch, grid, t):
+    """Every way a static call selects gives what the context does, and a context
+    call that needs the device to itself does not wait after it."""
+    prob = synth.make_problem("tiny", batch=batch, grid=grid, t=t, k=40)
+    wide = synth.make_problem("tiny", batch=1, grid=(1, 16, 24), t=560, k=40)
+    print(f"\n[case] static route: B={batch} N={prob.workload.n} T={t}", flush=True)
+    pr = make_pruner(prob, torch)
+    try:
+        x = _tensors(prob)
+        want = [o.clone() for o in pr.prune(*x, prob.k)[:3]]
+        cfg = binding.GmcConfig.from_buffer_copy(pr.cfg)
+        probe = to_device(prob.probe, prob.workload.dtype, torch)   # (outlives pr, which the last calls follow)
+        cfg.value_probe = probe.data_ptr()
+        go, out = _static_call(prob, cfg, x)
+        for o in out:
+            o.zero_()
+        go()
+        torch.cuda.synchronize()
+        assert torch.equal(out[2], want[2]) and torch.equal(out[1], want[1])
+        # the same members and fp32 sums in one order: only the assignment's
+        # gate could differ in its last bits
+        torch.testing.assert_close(out[0], want[0], rtol=1e-5, atol=1e-5)
+    finally:
+        pr.close()
+    pr = make_pruner(wide, torch)
+    try:
+        x = _tensors(wide)
+        pr.prune(*x, wide.k)
+        torch.cuda.synchronize()
+        go()
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        pr.prune(*x, wide.k)
+        torch.cuda.synchronize()
+        assert time.perf_counter() - t0 < 1.0   # (a turn that was not left costs 2 s)
+        code, _ = binding.gmc_get_diag(0)
+        assert code == binding.GMC_OK, binding.gmc_last_error()
     finally:
         pr.close()
